@@ -209,6 +209,25 @@ psc_status psc_conv3x3_fwd_strided(const psc_layer *layer, const psc_packed *pac
                                    int32_t relu, void *d_y, int32_t stride, int32_t algo,
                                    void *stream);
 
+/* psc_conv3x3_fwd (pool 0, stride 1), _pool2 (pool != 0) or _strided with a
+ * scratch buffer of the caller's, at least psc_conv3x3_workspace bytes and
+ * 256-byte aligned (NULL: exactly those calls).  With it algo 0 may run fp16
+ * layers on the matrix cores: each call then decodes the packed weights into
+ * the buffer and multiplies the dense tiles, with the same products and fp32
+ * sums.  The buffer holds nothing from one call to the next.  Calls on the
+ * same *packed may share one buffer, also on several streams (each writes the
+ * same bytes); calls on different ones that may overlap need one each. */
+psc_status psc_conv3x3_workspace(const psc_layer *layer, size_t *bytes);
+/* *out = 1 where psc_conv3x3_fwd_ws with algo 0 runs the matrix-core kernel
+ * (host only, arguments validated as by psc_conv3x3_config). */
+psc_status psc_conv3x3_on_matrix_cores(const psc_layer *layer, int32_t act_dtype, int32_t n,
+                                       int32_t h, int32_t w, int32_t pool, int32_t stride, int32_t *out);
+psc_status psc_conv3x3_fwd_ws(const psc_layer *layer, const psc_packed *packed,
+                              int32_t act_dtype, const void *d_x, int32_t n,
+                              int32_t h, int32_t w, const void *d_bias,
+                              int32_t relu, void *d_y, int32_t pool, int32_t stride,
+                              int32_t algo, void *d_ws, size_t ws_bytes, void *stream);
+
 /* ---- Retraining (Sec. 3.3): the user retrains the pruned model like a
  * dense one, except that the gradients of pruned weights are zero.  For the
  * layer y = W x of psc_conv3x3_fwd (before sigma; dy is the gradient at
@@ -310,7 +329,8 @@ psc_status psc_admm_dual(const psc_layer *layer, const float *d_v, const uint8_t
  * these arguments: which kernel runs and how work maps onto it.  Host only,
  * no device work; arguments are validated as by psc_conv3x3_fwd_strided
  * (pool != 0 as by psc_conv3x3_fwd_pool2, which needs stride 1), except that
- * no pointer is needed.  Meant for tests and benchmark reports. */
+ * no pointer is needed.  Meant for tests and benchmark reports.  It describes
+ * the vector-ALU kernels; psc_conv3x3_fwd_ws may use the matrix cores instead. */
 typedef struct psc_conv_config {
     int32_t kernel;            /* 0: tuned kernel, one output column per lane
                                   1: tuned kernel, 4 output columns per lane

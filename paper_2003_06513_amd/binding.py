@@ -98,6 +98,9 @@ def lib() -> ctypes.CDLL:
         "psc_probe_mfma": ([i32, i32, P, P], ctypes.c_int),
         "psc_conv3x3_fwd_pool2": ([LP, PP, i32, P, i32, i32, i32, P, i32, P, i32, P], ctypes.c_int),
         "psc_conv3x3_fwd_strided": ([LP, PP, i32, P, i32, i32, i32, P, i32, P, i32, i32, P], ctypes.c_int),
+        "psc_conv3x3_workspace": ([LP, ctypes.POINTER(sz)], ctypes.c_int),
+        "psc_conv3x3_on_matrix_cores": ([LP, i32, i32, i32, i32, i32, i32, ctypes.POINTER(i32)], ctypes.c_int),
+        "psc_conv3x3_fwd_ws": ([LP, PP, i32, P, i32, i32, i32, P, i32, P, i32, i32, i32, P, sz, P], ctypes.c_int),
         "psc_conv3x3_config": ([LP, i32, i32, i32, i32, i32, i32, i32, ctypes.POINTER(CConvConfig)],
                                ctypes.c_int),
         "psc_transpose_layer": ([LP, LP], ctypes.c_int),
@@ -196,13 +199,17 @@ class Packed:
         self.cin_idx = torch.empty(keep, dtype=torch.int32, device=device)
         self.pat_id = torch.empty(keep, dtype=torch.uint8, device=device)
         self.values = torch.empty(keep * 4, dtype=vdt, device=device)
+        # scratch of the convolution calls on this storage (None: they need
+        # none); every call writes it anew
+        b = ctypes.c_size_t(0)
+        _check(lib().psc_conv3x3_workspace(layer.ref(), ctypes.byref(b)), "psc_conv3x3_workspace")
+        self.work_bytes = int(b.value)
+        self.work = torch.empty(b.value, dtype=torch.uint8, device=device) if b.value else None
 
     def c(self) -> CPacked:
-        cp = CPacked()
-        for n in PACKED_FIELDS:
-            t = getattr(self, n)
-            setattr(cp, n, t.data_ptr() if t.numel() else None)
-        return cp
+        # an empty tensor's address is 0: NULL
+        return CPacked(self.filter_perm.data_ptr(), self.filter_ptr.data_ptr(), self.seg_ptr.data_ptr(),
+                       self.cin_idx.data_ptr(), self.pat_id.data_ptr(), self.values.data_ptr())
 
     def to_host(self) -> dict:
         return {n: getattr(self, n).cpu().numpy() for n in PACKED_FIELDS}
@@ -265,15 +272,21 @@ def unpack_dense(layer: Layer, packed: Packed, w_dense, stream=None):
                                   _stream(stream)), "psc_unpack_dense")
 
 
+def _conv(layer, packed, x, n, h, w, y, bias, relu, pool, stride, algo, stream, where):
+    """psc_conv3x3_fwd_ws with the scratch that the storage carries."""
+    cp, ws = packed.c(), packed.work
+    _check(lib().psc_conv3x3_fwd_ws(layer.c, cp, dtype_code(x), _dev(x, "x"), n, h, w, _dev(bias, "bias"),
+                                    int(bool(relu)), _dev(y, "y"), pool, stride, int(algo),
+                                    None if ws is None else ws.data_ptr(), packed.work_bytes, _stream(stream)),
+           where)
+
+
 def conv3x3_fwd(layer: Layer, packed: Packed, x, y, bias=None, relu: bool = False, algo: int = 0,
                 stream=None):
     n, cin, h, w = (int(d) for d in x.shape)
     if cin != layer.cin or tuple(y.shape) != (n, layer.cout, h, w):
         raise ValueError("x/y shapes do not match the layer")
-    cp = packed.c()
-    _check(lib().psc_conv3x3_fwd_algo(layer.ref(), ctypes.byref(cp), dtype_code(x), _dev(x, "x"), n, h,
-                                      w, _dev(bias, "bias"), int(bool(relu)), _dev(y, "y"), int(algo),
-                                      _stream(stream)), "psc_conv3x3_fwd")
+    _conv(layer, packed, x, n, h, w, y, bias, relu, 0, 1, algo, stream, "psc_conv3x3_fwd")
 
 
 def conv3x3_fwd_pool2(layer: Layer, packed: Packed, x, y, bias=None, relu: bool = False, algo: int = 0,
@@ -283,10 +296,7 @@ def conv3x3_fwd_pool2(layer: Layer, packed: Packed, x, y, bias=None, relu: bool 
     n, cin, h, w = (int(d) for d in x.shape)
     if cin != layer.cin or tuple(y.shape) != (n, layer.cout, h // 2, w // 2):
         raise ValueError("x/y shapes do not match the layer and the 2x2 pool")
-    cp = packed.c()
-    _check(lib().psc_conv3x3_fwd_pool2(layer.ref(), ctypes.byref(cp), dtype_code(x), _dev(x, "x"), n, h,
-                                       w, _dev(bias, "bias"), int(bool(relu)), _dev(y, "y"), int(algo),
-                                       _stream(stream)), "psc_conv3x3_fwd_pool2")
+    _conv(layer, packed, x, n, h, w, y, bias, relu, 1, 1, algo, stream, "psc_conv3x3_fwd_pool2")
 
 
 def conv3x3_fwd_strided(layer: Layer, packed: Packed, x, y, stride: int, bias=None, relu: bool = False,
@@ -298,10 +308,7 @@ def conv3x3_fwd_strided(layer: Layer, packed: Packed, x, y, stride: int, bias=No
         raise ValueError("stride must be 1 or 2")
     if cin != layer.cin or tuple(y.shape) != (n, layer.cout, (h - 1) // stride + 1, (w - 1) // stride + 1):
         raise ValueError("x/y shapes do not match the layer and the stride")
-    cp = packed.c()
-    _check(lib().psc_conv3x3_fwd_strided(layer.ref(), ctypes.byref(cp), dtype_code(x), _dev(x, "x"), n, h, w,
-                                         _dev(bias, "bias"), int(bool(relu)), _dev(y, "y"), stride,
-                                         int(algo), _stream(stream)), "psc_conv3x3_fwd_strided")
+    _conv(layer, packed, x, n, h, w, y, bias, relu, 0, stride, algo, stream, "psc_conv3x3_fwd_strided")
 
 
 def conv3x3_config(layer: Layer, dtype: int, n: int, h: int, w: int, pool: bool = False, stride: int = 1,
@@ -311,6 +318,16 @@ def conv3x3_config(layer: Layer, dtype: int, n: int, h: int, w: int, pool: bool 
     _check(lib().psc_conv3x3_config(layer.ref(), int(dtype), int(n), int(h), int(w), int(bool(pool)),
                                     int(stride), int(algo), ctypes.byref(c)), "psc_conv3x3_config")
     return {name: int(getattr(c, name)) for name, _ in CConvConfig._fields_}
+
+
+def conv3x3_on_matrix_cores(layer: Layer, dtype: int, n: int, h: int, w: int, pool: bool = False,
+                            stride: int = 1) -> bool:
+    """psc_conv3x3_on_matrix_cores: whether a conv call with algo 0 runs the
+    matrix-core kernel (host only)."""
+    out = ctypes.c_int32(0)
+    _check(lib().psc_conv3x3_on_matrix_cores(layer.ref(), int(dtype), int(n), int(h), int(w), int(bool(pool)),
+                                             int(stride), ctypes.byref(out)), "psc_conv3x3_on_matrix_cores")
+    return bool(out.value)
 
 
 def dense3x3_fwd(x, wd, y, bias=None, relu: bool = False, stream=None):

@@ -1,0 +1,543 @@
+// The pattern-sparse 3x3 convolution (Sec. 4.1 Eq. 1) on the matrix cores,
+// for fp16 calls of enough output pixels: an implicit GEMM with M = reordered
+// filters, N = output pixels and K = (channel, tap), in two launches.
+//   k_weight_tiles  decodes the compressed storage (Sec. 3.4) into dense tiles
+//                   in the order in which the next kernel stages them,
+//   k_conv_mfma     multiplies them.
+//
+// Why dense tiles of a sparse layer: a kept kernel is 4 taps of 9, so they
+// cost 9 / (4 keep) times the multiply-adds (5.6 at keep 0.4), but
+// v_mfma_f32_32x32x16_f16 does 16 times those of v_fmac_f32 a clock, and a
+// staged input feeds all filters of the block.  The vector kernels are bound
+// by the vector-memory path that brings each kernel's rows to the registers.
+// Measured (fp16, 60 % dropped, us a call, vector kernel first):
+// 512 @ 28x28 b64 866 -> 247, 512 @ 7x7 b32 42.5 -> 29.8, 256 @ 14x14 b32
+// 36.1 -> 22.7, 128 @ 28x28 b32 48.0 -> 20.3, 64 @ 56x56 b32 49.4 -> 24.0.
+// Decoding inside the convolution instead (each block scattering its filters'
+// kernels into its weight tile) measured 342 on the first and 62 on the
+// second: the scatter repeats for every pixel tile.
+//
+// A block owns kF filters x NT output pixels (consecutive in raster order
+// over the images of a column strip).  Per stage, G groups of 4 waves take 32
+// channels each from LDS:
+//   X[c / 8][position][8]       the input rows the tile needs, channels innermost,
+//   A[c / 32][tap][c / 8][filter][8]   the weights,
+// both in 16-byte units that neighbouring lanes read from neighbouring
+// addresses (no bank conflicts).  A tap is an offset of positions, so one X
+// tile serves all nine.  The next stage's values load into registers while
+// the MFMAs of this one run; the large tiles are bound by LDS reads (4 KB for
+// 4 MFMAs of a wave, the 128 B a clock that LDS gives), the small ones by the
+// latency of their chain of stages.
+//
+// Infinities and NaNs: the dense tile multiplies pruned weights (zero) by
+// every staged input, which must not turn a non-finite input that no kept
+// weight reads into NaN.  A block that staged a non-finite value computes its
+// outputs again with the sum over the kept weights alone.
+//
+// Layout of v_mfma_f32_32x32x16_f16: lane l supplies A[l % 32][8 (l / 32) + j]
+// and B[8 (l / 32) + j][l % 32], j = 0..7; register r of the result holds
+// D[8 (r / 4) + 4 (l / 32) + r % 4][l % 32].
+#include <cstring>
+
+#include "common.h"
+#include "launch.h"
+
+namespace psc {
+namespace {
+
+constexpr int kF = 64;         // filters per block
+constexpr int kKC = 32, kQ = kKC / 8;   // channels of a weight chunk and per four waves and stage
+
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+typedef float f16v __attribute__((ext_vector_type(16)));
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+
+struct MGeo {
+    int n, cin, H, W, cout, m, relu, keep;
+    int S;              // stride
+    int OH, OW;
+    int CT, TW;         // column strips and output columns of one
+    int P;              // positions of a tile row: S * TW + 2
+    int Lst;            // positions of the X tile (its stride between channel groups)
+    int slots;          // output slots of a strip: n * OH * TW
+    int ptiles;         // pixel tiles of a strip
+    int ftiles;
+    int nblocks;
+    int chunks;         // 32-channel chunks of the weight tiles: an even number
+    int x_bytes;
+    uint16_t taps[kMaxPatterns];   // a pattern's 4 taps, 4 bits each, ascending
+};
+
+// The weight tiles of a call, decoded from the compressed storage:
+//   wt[f / 64][c / 32][tap][(c / 8) % 4][f % 64][c % 8],
+// zero where pruned and past cin and cout; f counts reordered filters.  A
+// block owns 8 filters x 128 channels: its waves scan their 2 filters'
+// kernels, scatter the weights to LDS and write 16-byte units.
+constexpr int kDF = 8, kDC = 128;
+
+__global__ __launch_bounds__(256) void k_weight_tiles(const int32_t* __restrict__ fptr,
+                                                      const int32_t* __restrict__ cin_idx,
+                                                      const uint8_t* __restrict__ pat_id,
+                                                      const uint16_t* __restrict__ values, MGeo g,
+                                                      uint16_t* __restrict__ wt) {
+    __shared__ __align__(16) uint16_t t[kDF][9 * kDC];
+    const int f0 = blockIdx.x * kDF, c0 = blockIdx.y * kDC;
+    for (int e = threadIdx.x; e < kDF * 9 * kDC / 8; e += 256) reinterpret_cast<u4*>(t)[e] = u4{0, 0, 0, 0};
+    __syncthreads();
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int i = 0; i < 2; ++i) {
+        const int fl = 2 * wave + i;
+        if (f0 + fl >= g.cout) continue;
+        const int k0 = fptr[f0 + fl] > 0 ? fptr[f0 + fl] : 0;
+        const int k1 = fptr[f0 + fl + 1] < g.keep ? fptr[f0 + fl + 1] : g.keep;
+        for (int k = k0 + lane; k < k1; k += 64) {
+            const int c = cin_idx[k] - c0, p = pat_id[k];
+            if (uint32_t(c) >= uint32_t(kDC) || c0 + c >= g.cin || p >= g.m) continue;
+            uint32_t v[2];
+            __builtin_memcpy(v, values + 4 * int64_t(k), 8);
+            const uint32_t tp = g.taps[p];
+            t[fl][(tp & 15) * kDC + c] = uint16_t(v[0]);
+            t[fl][((tp >> 4) & 15) * kDC + c] = uint16_t(v[0] >> 16);
+            t[fl][((tp >> 8) & 15) * kDC + c] = uint16_t(v[1]);
+            t[fl][(tp >> 12) * kDC + c] = uint16_t(v[1] >> 16);
+        }
+    }
+    __syncthreads();
+    // unit (filter, tap, 8 channels): neighbouring lanes take the 8 filters
+    const int nst = g.chunks;
+    for (int e = threadIdx.x; e < kDF * 9 * kDC / 8; e += 256) {
+        const int fl = e % kDF, u = e / kDF, cg = u % (kDC / 8), q = u / (kDC / 8);
+        const int f = f0 + fl, st = c0 / kKC + cg / (kKC / 8);
+        if (st >= nst) continue;
+        const int64_t at = (((int64_t(f / kF) * nst + st) * 9 + q) * (kKC / 8) + cg % (kKC / 8)) * kF + f % kF;
+        reinterpret_cast<u4*>(wt)[at] = *reinterpret_cast<const u4*>(&t[fl][q * kDC + cg * 8]);
+    }
+}
+
+template <int NT, int G, bool ALIGNED, int MI>
+__global__ __launch_bounds__(256 * G, 2) void k_conv_mfma(
+    const uint16_t* __restrict__ x, const uint16_t* __restrict__ wtiles, const int32_t* __restrict__ perm,
+    const int32_t* __restrict__ fptr, const int32_t* __restrict__ cin_idx, const uint8_t* __restrict__ pat_id,
+    const uint16_t* __restrict__ values, const uint16_t* __restrict__ bias, MGeo g, uint16_t* __restrict__ y) {
+    constexpr int kThreads = 256 * G, KC = kKC * G, KQ = KC / 8;
+    // four waves each take 32 channels of a stage: 256 pixels: 4 of 64 filters x 64 pixels; 128: 2 x 2 of 32 x 64;
+    // 64: 2 x 2 of 32 x 32
+    constexpr int WF = NT == 256 ? 1 : 2, WN = 4 / WF;
+    constexpr int FI = kF / WF / 32, NI = NT / WN / 32;
+    extern __shared__ __align__(16) char lds[];
+    char* const ldsA = lds;                              // 9 * KQ * kF * 16 bytes
+    char* const ldsX = lds + 9 * KQ * kF * 16;           // KQ * Lst * 16 bytes
+    __shared__ int perm_s[kF];
+    __shared__ float bias_s[kF];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = (tid >> 6) & 3, grp = tid >> 8;
+    // blocks go to the 8 XCDs in turn: an XCD takes consecutive tiles, pixels
+    // first, so that its L2 holds few filters' weights (512 @ 7x7 b32: 34.2 us
+    // with filters first, 29.8 so)
+    const int per = (g.nblocks + 7) / 8;
+    const int b = int(blockIdx.x % 8) * per + int(blockIdx.x / 8);
+    if (b >= g.nblocks || int(blockIdx.x / 8) >= per) return;
+    const int pts = g.ptiles * g.CT;
+    const int ft = b / pts, pt = b - ft * pts;
+    const int strip = pt / g.ptiles, o0 = (pt - strip * g.ptiles) * NT;
+    const int j0 = strip * g.TW;                         // first output column of the strip
+    const int f0 = ft * kF;
+    const int plane = g.H * g.W, rowp = g.H + 1, per_img = g.OH * g.TW;
+
+    // the tile's rows: padded row img * (H + 1) + i + 1 holds image row i
+    auto prow = [&](int o, int& img, int& i, int& j) {
+        img = o / per_img;
+        const int r = o - img * per_img;
+        i = r / g.TW;
+        j = r - i * g.TW;
+        return img * rowp + g.S * i + 1;
+    };
+    int img, i, j;
+    const int olast = (o0 + NT < g.slots ? o0 + NT : g.slots) - 1;
+    const int row_lo = prow(o0, img, i, j) - 1;
+    const int rows = prow(olast, img, i, j) + 1 - row_lo + 1;
+
+    // this lane's output pixels
+    int xbase[NI], ybase[NI];
+    bool live[NI];
+    const int wf = (wave % WF) * (kF / WF), wn = (wave / WF) * (NT / WN);
+#pragma unroll
+    for (int t = 0; t < NI; ++t) {
+        const int o = o0 + wn + 32 * t + (lane & 31);
+        live[t] = o < g.slots;
+        const int pr = prow(live[t] ? o : olast, img, i, j);
+        live[t] = live[t] && j0 + j < g.OW;
+        xbase[t] = ((pr - 1 - row_lo) * g.P + g.S * j + (lane >> 5) * g.Lst) * 16;
+        ybase[t] = img * g.cout * g.OH * g.OW + i * g.OW + j0 + j;
+    }
+
+    // zero the X tile once: padding rows and columns are never written
+    for (int e = tid; e < KQ * g.Lst; e += kThreads) *reinterpret_cast<u4*>(ldsX + e * 16) = u4{0, 0, 0, 0};
+    if (tid < kF) {
+        const int p = f0 + tid < g.cout ? perm[f0 + tid] : -1;
+        perm_s[tid] = p;
+        bias_s[tid] = bias && p >= 0 ? Elt<DT_F16>::load(bias, p) : 0.f;
+    }
+
+    // staging slots of this thread: 4 columns x 8 channels.  The last vector
+    // of a row ends with the row (or the strip) and may overlap the one before
+    const auto xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(x), int16_t(0), g.x_bytes, 0x00020000);
+    uint32_t goff[MI];
+    int loff[MI];
+    const int tw = g.S * g.TW, nv = (tw + 3) / 4, items = KQ * rows * nv;
+    {
+        const int cols = g.W - g.S * j0 < tw ? g.W - g.S * j0 : tw;      // at least 4
+#pragma unroll
+        for (int s = 0; s < MI; ++s) {
+            const int e = tid + kThreads * s;
+            goff[s] = 0x80000000u;
+            loff[s] = -1;
+            if (e < items) {
+                const int v = e % nv, r = (e / nv) % rows, kq = e / (nv * rows);
+                const int gr = row_lo + r, im = gr / rowp, ir = gr - im * rowp - 1;
+                const int rel = 4 * v < cols - 4 ? 4 * v : cols - 4;
+                if (ir >= 0 && im < g.n && 4 * v < cols) {
+                    goff[s] = uint32_t((im * g.cin + 8 * kq) * plane + ir * g.W + g.S * j0 + rel) * 2u;
+                    loff[s] = (kq * g.Lst + r * g.P + 1 + rel) * 16;
+                }
+            }
+        }
+    }
+    // halo columns of a strip: one column x 8 channels
+    const bool halo = g.CT > 1;
+    uint32_t hgoff = 0x80000000u;
+    int hloff = -1;
+    if (halo && tid < KQ * rows * 2) {
+        const int side = tid & 1, r = (tid >> 1) % rows, kq = (tid >> 1) / rows;
+        const int gr = row_lo + r, im = gr / rowp, ir = gr - im * rowp - 1;
+        const int col = side ? g.S * (j0 + g.TW) : g.S * j0 - 1;
+        if (ir >= 0 && im < g.n && col >= 0 && col < g.W) {
+            hgoff = uint32_t((im * g.cin + 8 * kq) * plane + ir * g.W + col) * 2u;
+            hloff = (kq * g.Lst + r * g.P + (side ? g.P - 1 : 0)) * 16;
+        }
+    }
+    u2 xv[MI][8];
+    uint32_t hv[8];
+    uint32_t bad = 0;
+    auto fetch = [&](int c0) {
+        // channels past cin read what follows (their weights are zero) or,
+        // past x, zero
+        const uint32_t so = uint32_t(c0 * plane) * 2u, cs = uint32_t(plane) * 2u;
+#pragma unroll
+        for (int s = 0; s < MI; ++s) {
+            if (kThreads * s >= items) continue;         // the same for the whole block
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                const uint32_t vo = goff[s] + (so + uint32_t(c) * cs);
+                if constexpr (ALIGNED) {
+                    xv[s][c] = __builtin_amdgcn_raw_buffer_load_b64(xr, int(vo), 0, 0);
+                } else {
+                    xv[s][c] = u2{0, 0};
+                    if (vo + 8u <= uint32_t(g.x_bytes))
+                        __builtin_memcpy(&xv[s][c], reinterpret_cast<const char*>(x) + vo, 8);
+                }
+            }
+        }
+        if (halo) {
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+                hv[c] = __builtin_amdgcn_raw_buffer_load_b16(xr, int(hgoff + (so + uint32_t(c) * cs)), 0, 0);
+        }
+    };
+    // exponent all ones in either half sets bit 15 or 31
+    auto test = [&](uint32_t w) { bad |= (w & 0x7c007c00u) + 0x04000400u; };
+    auto stage_x = [&]() {
+#pragma unroll
+        for (int s = 0; s < MI; ++s) {
+            if (loff[s] < 0) continue;
+            uint32_t w[2][8];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                w[0][c] = xv[s][c].x;
+                w[1][c] = xv[s][c].y;
+                test(w[0][c]);
+                test(w[1][c]);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                u4 o;
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    o[c] = __builtin_amdgcn_perm(w[e / 2][2 * c + 1], w[e / 2][2 * c],
+                                                 e & 1 ? 0x07060302u : 0x05040100u);
+                *reinterpret_cast<u4*>(ldsX + loff[s] + e * 16) = o;
+            }
+        }
+        if (halo && hloff >= 0) {
+            u4 o;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                o[c] = __builtin_amdgcn_perm(hv[2 * c + 1], hv[2 * c], 0x05040100u);
+                test(o[c]);
+            }
+            *reinterpret_cast<u4*>(ldsX + hloff) = o;
+        }
+    };
+
+    // the stage's weight tile: 36 KiB in the LDS order, 9 x 16 bytes a thread
+    constexpr int AJ = 9 * KQ * kF / kThreads;
+    const int nst = g.chunks / G;
+    const u4* const wt = reinterpret_cast<const u4*>(wtiles) + int64_t(ft) * nst * (AJ * kThreads) + tid;
+    u4 wv[AJ];
+    auto fetch_a = [&](int st) {
+#pragma unroll
+        for (int e = 0; e < AJ; ++e) wv[e] = wt[int64_t(st) * (AJ * kThreads) + e * kThreads];
+    };
+    auto stage_a = [&]() {
+#pragma unroll
+        for (int e = 0; e < AJ; ++e) *reinterpret_cast<u4*>(ldsA + (tid + e * kThreads) * 16) = wv[e];
+    };
+
+    f16v acc[FI][NI];
+#pragma unroll
+    for (int a = 0; a < FI; ++a)
+#pragma unroll
+        for (int t = 0; t < NI; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[a][t][r] = 0.f;
+
+    const char* const abase = ldsA + (grp * 9 * kQ * kF + (lane >> 5) * kF + wf + (lane & 31)) * 16;
+    const char* const xgrp = ldsX + grp * kQ * g.Lst * 16;
+    auto mfma = [&](int ks) {                            // 16 channels, nine taps
+        const char* xk = xgrp + 2 * ks * g.Lst * 16;
+        const char* const ak = abase + 2 * ks * kF * 16;
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+#pragma unroll
+            for (int s = 0; s < 3; ++s) {
+                h8 av[FI], bv[NI];
+#pragma unroll
+                for (int a = 0; a < FI; ++a)
+                    av[a] = *reinterpret_cast<const h8*>(ak + ((3 * r + s) * kQ * kF + 32 * a) * 16);
+#pragma unroll
+                for (int t = 0; t < NI; ++t) bv[t] = *reinterpret_cast<const h8*>(xk + xbase[t] + s * 16);
+#pragma unroll
+                for (int a = 0; a < FI; ++a)
+#pragma unroll
+                    for (int t = 0; t < NI; ++t)
+                        acc[a][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[a], bv[t], acc[a][t], 0, 0, 0);
+            }
+            xk += g.P * 16;
+        }
+    };
+    fetch(0);
+    fetch_a(0);
+    __syncthreads();                                     // X zeroed
+    for (int c0 = 0; c0 < g.cin; c0 += KC) {
+        stage_x();
+        stage_a();
+        __syncthreads();
+        if (c0 + KC < g.cin) {                           // in flight during the MFMAs
+            fetch(c0 + KC);
+            fetch_a(c0 / KC + 1);
+        }
+#pragma unroll
+        for (int ks = 0; ks < kKC / 16; ++ks) mfma(ks);
+        __syncthreads();
+    }
+
+    // one staged value of the block not finite: sum the kept weights alone
+    if (__syncthreads_or(int(bad & 0x80008000u))) {
+        for (int e = tid; e < kF * NT; e += kThreads) {
+            const int f = e / NT, o = o0 + e % NT;
+            if (f0 + f >= g.cout || o >= g.slots) continue;
+            prow(o, img, i, j);
+            if (j0 + j >= g.OW) continue;
+            float s = 0.f;
+            const int k1 = fptr[f0 + f + 1] < g.keep ? fptr[f0 + f + 1] : g.keep;
+            for (int k = fptr[f0 + f] > 0 ? fptr[f0 + f] : 0; k < k1; ++k) {
+                const int c = cin_idx[k], p = pat_id[k];
+                if (uint32_t(c) >= uint32_t(g.cin) || p >= g.m) continue;
+                const uint32_t tp4 = g.taps[p];
+                const uint16_t* xp = x + (int64_t(img) * g.cin + c) * plane;
+                for (int t = 0; t < 4; ++t) {
+                    const int q = (tp4 >> (4 * t)) & 15;
+                    const int ih = g.S * i + q / 3 - 1, iw = g.S * (j0 + j) + q % 3 - 1;
+                    if (ih >= 0 && ih < g.H && iw >= 0 && iw < g.W)
+                        s = fmaf(Elt<DT_F16>::load(values, 4 * int64_t(k) + t), Elt<DT_F16>::load(xp, ih * g.W + iw), s);
+                }
+            }
+            s += bias_s[f];
+            if (g.relu) s = s > 0.f ? s : 0.f;
+            y[(int64_t(img) * g.cout + perm_s[f]) * g.OH * g.OW + i * g.OW + j0 + j] = Elt<DT_F16>::from_f(s);
+        }
+        return;
+    }
+
+    // the second group's sums go to the first through LDS
+    if constexpr (G == 2) {
+        float* const red = reinterpret_cast<float*>(lds) + wave * (FI * NI * 1024) + lane;
+#pragma unroll
+        for (int a = 0; a < FI; ++a)
+#pragma unroll
+            for (int t = 0; t < NI; ++t)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (grp) red[((a * NI + t) * 16 + r) * 64] = acc[a][t][r];
+        __syncthreads();
+        if (grp) return;
+#pragma unroll
+        for (int a = 0; a < FI; ++a)
+#pragma unroll
+            for (int t = 0; t < NI; ++t)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[a][t][r] += red[((a * NI + t) * 16 + r) * 64];
+    }
+    const int oplane = g.OH * g.OW;
+#pragma unroll
+    for (int a = 0; a < FI; ++a)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int f = wf + 32 * a + 8 * (r / 4) + 4 * (lane >> 5) + r % 4;
+            if (f0 + f >= g.cout) continue;
+            const float bv = bias_s[f];
+            uint16_t* const yf = y + int64_t(perm_s[f]) * oplane;
+#pragma unroll
+            for (int t = 0; t < NI; ++t)
+                if (live[t]) {
+                    float v = acc[a][t][r] + bv;
+                    if (g.relu) v = v > 0.f ? v : 0.f;
+                    yf[ybase[t]] = Elt<DT_F16>::from_f(v);
+                }
+        }
+}
+
+// The pixel tile and geometry of a call; false when the kernel does not take
+// it.  Host only.
+struct MPlan {
+    MGeo g;
+    int NT, G, MI;
+    bool aligned;
+    size_t lds;
+};
+
+bool tile_plan(const ConvArgs& a, int m, int NT, int G, MPlan& p) {
+    const int kThreads = 256 * G, KC = kKC * G;
+    MGeo& g = p.g;
+    g.n = a.n;
+    g.cin = a.cin;
+    g.H = a.h;
+    g.W = a.w;
+    g.cout = a.cout;
+    g.m = m;
+    g.relu = a.relu;
+    g.keep = int(a.keep);
+    g.chunks = (a.cin + 63) / 64 * 2;
+    g.S = a.stride;
+    g.OH = (a.h - 1) / a.stride + 1;
+    g.OW = (a.w - 1) / a.stride + 1;
+    g.x_bytes = int(int64_t(a.n) * a.cin * a.h * a.w * 2);
+    // strips of at most 32 output columns; 4-column loads are aligned where
+    // rows and strips are multiples of 4 columns
+    g.CT = (g.OW + 31) / 32;
+    g.TW = (g.OW + g.CT - 1) / g.CT;
+    p.aligned = a.w % 4 == 0 && reinterpret_cast<uintptr_t>(a.x) % 8 == 0;
+    if (p.aligned && g.CT > 1) g.TW = (g.TW + 3) / 4 * 4;
+    g.CT = (g.OW + g.TW - 1) / g.TW;
+    if (a.w - g.S * (g.CT - 1) * g.TW < 4) return false;     // a strip narrower than one vector
+    g.P = g.S * g.TW + 2;
+    const int64_t slots = int64_t(a.n) * g.OH * g.TW;
+    if (slots * g.CT > 0x3fffffff) return false;
+    g.slots = int(slots);
+    g.ptiles = int((slots + NT - 1) / NT);
+    g.ftiles = (a.cout + kF - 1) / kF;
+    const int64_t blocks = int64_t(g.ptiles) * g.CT * g.ftiles;
+    if (blocks > 0x3fffffff) return false;
+    g.nblocks = int(blocks);
+    // padded rows of the largest tile: NT slots touch at most orows output
+    // rows and cross at most `cross` image boundaries
+    int64_t orows = (NT - 2) / g.TW + 2;
+    if (orows > int64_t(a.n) * g.OH) orows = int64_t(a.n) * g.OH;
+    const int64_t cross = (orows + g.OH - 2) / g.OH;
+    const int64_t rows = g.S * (orows - 1) + 3 + cross * (a.h + 1 - g.S * g.OH);
+    g.Lst = int(rows * g.P);
+    const int64_t items = (KC / 8) * rows * ((g.S * g.TW + 3) / 4);
+    const int64_t per = (items + kThreads - 1) / kThreads;
+    p.MI = per <= 2 ? 2 : 4;
+    if (per > p.MI || (g.CT > 1 && (KC / 8) * rows * 2 > kThreads)) return false;
+    p.NT = NT;
+    p.G = G;
+    p.lds = size_t(9 * (KC / 8) * kF * 16) + size_t(KC / 8) * g.Lst * 16;
+    return p.lds <= 136 * 1024;
+}
+
+bool plan_conv_mfma(const PatTable& tab, const ConvArgs& a, MPlan& p) {
+    if (a.dtype != DT_F16 || a.pool || a.cin < 16 || a.cout < 32) return false;
+    // 32-bit byte offsets into x, and up to 64 channels past it
+    if ((int64_t(a.n) * a.cin + 64) * a.h * a.w * 2 >= (int64_t(1) << 31) || a.keep > 0x0fffffff) return false;
+    // Against the vector kernels: those take about 7 us and 30 TFLOP/s of
+    // nonzero multiply-adds on small and middle calls (48 on the largest);
+    // this path about 6 us (two launches) and the larger of 3 us per 64
+    // channels (the latency of one tile's chain of stages) and 700 TFLOP/s of
+    // dense work.  Measured both ways on 30 layers; those within 15 % stay.
+    const double outs = double(a.n) * ((a.h - 1) / a.stride + 1) * ((a.w - 1) / a.stride + 1);
+    const double valu_us = 7.0 + 8.0 * outs * double(a.keep) / 30e6;
+    const double dense_us = 18.0 * outs * a.cin * a.cout / 700e6, chain_us = 3.0 * ((a.cin + 63) / 64);
+    if (1.15 * (6.0 + (dense_us > chain_us ? dense_us : chain_us)) > valu_us) return false;
+    std::memset(&p, 0, sizeof p);
+    for (int i = 0; i < tab.m; ++i) {
+        uint32_t t = 0, k = 0;
+        for (uint32_t q = 0; q < 9; ++q)
+            if ((tab.mask[i] >> q) & 1) t |= q << (4 * k++);
+        p.g.taps[i] = uint16_t(t);
+    }
+    // The largest tile that still gives each CU about 1.5 blocks (2 fit);
+    // else about one block per CU, of 8 waves that take 64 channels a stage
+    // (256 @ 14x14 at batch 32: 22.7 us, against 24.5 in 4-wave blocks of half
+    // the pixels; 512 @ 7x7: 29.8 against 33.7).
+    if (tile_plan(a, tab.m, 256, 1, p) && p.g.nblocks >= 384) return true;
+    if (tile_plan(a, tab.m, 128, 1, p) && p.g.nblocks >= 384) return true;
+    if (p.g.nblocks >= 160 && p.g.nblocks <= 256 && tile_plan(a, tab.m, 128, 2, p)) return true;
+    if (tile_plan(a, tab.m, 64, 2, p) && p.g.nblocks <= 256) return true;
+    return tile_plan(a, tab.m, 64, 1, p);
+}
+
+template <int NT, int G, bool ALIGNED, int MI>
+hipError_t launch(const MPlan& p, const PackedView& pk, const ConvArgs& a, hipStream_t s) {
+    const int grid = (p.g.nblocks + 7) / 8 * 8;
+    hipLaunchKernelGGL((k_conv_mfma<NT, G, ALIGNED, MI>), dim3(unsigned(grid)), dim3(256 * G), unsigned(p.lds), s,
+                       static_cast<const uint16_t*>(a.x), static_cast<const uint16_t*>(a.ws), pk.filter_perm,
+                       pk.filter_ptr, pk.cin_idx, pk.pat_id, static_cast<const uint16_t*>(pk.values),
+                       static_cast<const uint16_t*>(a.bias), p.g, static_cast<uint16_t*>(a.y));
+    return hipGetLastError();
+}
+
+template <int NT, int G>
+hipError_t launch_nt(const MPlan& p, const PackedView& pk, const ConvArgs& a, hipStream_t s) {
+    if (p.aligned) return p.MI == 2 ? launch<NT, G, true, 2>(p, pk, a, s) : launch<NT, G, true, 4>(p, pk, a, s);
+    return p.MI == 2 ? launch<NT, G, false, 2>(p, pk, a, s) : launch<NT, G, false, 4>(p, pk, a, s);
+}
+
+}  // namespace
+
+size_t conv_workspace_bytes(int dtype, int cout, int cin) {
+    if (dtype != DT_F16 || cin < 16 || cout < 32) return 0;
+    return size_t((cout + kF - 1) / kF) * size_t((cin + 63) / 64 * 2) * (9 * kKC * kF * 2);
+}
+
+bool conv_mfma_takes(const PatTable& tab, const ConvArgs& a) {
+    MPlan p;
+    return plan_conv_mfma(tab, a, p);
+}
+
+hipError_t launch_conv_mfma(const PatTable& tab, const PackedView& pk, const ConvArgs& a, hipStream_t s) {
+    MPlan p;
+    if (!a.ws || a.ws_bytes < conv_workspace_bytes(a.dtype, a.cout, a.cin) || !plan_conv_mfma(tab, a, p))
+        return hipErrorNotSupported;
+    const dim3 grid(unsigned((p.g.ftiles * kF) / kDF), unsigned((a.cin + kDC - 1) / kDC));
+    hipLaunchKernelGGL(k_weight_tiles, grid, dim3(256), 0, s, pk.filter_ptr, pk.cin_idx, pk.pat_id,
+                       static_cast<const uint16_t*>(pk.values), p.g, static_cast<uint16_t*>(a.ws));
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (p.NT == 256) return launch_nt<256, 1>(p, pk, a, s);
+    if (p.NT == 128) return p.G == 1 ? launch_nt<128, 1>(p, pk, a, s) : launch_nt<128, 2>(p, pk, a, s);
+    return p.G == 1 ? launch_nt<64, 1>(p, pk, a, s) : launch_nt<64, 2>(p, pk, a, s);
+}
+
+}  // namespace psc

@@ -14,6 +14,7 @@ bool describe_conv_stride2(const PatTable& tab, const ConvArgs& a, ConvForm& out
 hipError_t launch_conv_rows(const PatTable& tab, const PackedView& pk, const ConvArgs& a, hipStream_t stream);
 bool describe_conv_rows(const PatTable& tab, const ConvArgs& a, ConvForm& out);
 bool prefer_conv_rows(const PatTable& tab, const ConvArgs& a);
+hipError_t launch_conv_mfma(const PatTable& tab, const PackedView& pk, const ConvArgs& a, hipStream_t stream);
 
 namespace {
 
@@ -358,6 +359,10 @@ hipError_t conv_simple(const PatTable& tab, const PackedView& pk, const ConvArgs
 
 hipError_t launch_conv(const PatTable& tab, const PackedView& pk, const ConvArgs& a, int algo,
                        hipStream_t stream) {
+    if (algo == 0) {
+        const hipError_t e = launch_conv_mfma(tab, pk, a, stream);
+        if (e != hipErrorNotSupported) return e;
+    }
     // algo 2: the one-row-per-lane kernel (the caller has checked that it
     // takes the call)
     if (algo == 2 || (algo == 0 && prefer_conv_rows(tab, a))) return launch_conv_rows(tab, pk, a, stream);

@@ -61,9 +61,17 @@ struct ConvArgs {
     void* y;
     int pool;       // 1: y is the 2x2/2 max-pool of sigma(conv), [n][cout][h/2][w/2]
     int stride = 1; // 1 or 2 (zero padding 1): y is [n][cout][(h-1)/stride+1][(w-1)/stride+1]
+    void* ws = nullptr;     // scratch for the matrix-core kernel, or none
+    size_t ws_bytes = 0;
 };
 hipError_t launch_conv(const PatTable& tab, const PackedView& pk, const ConvArgs& a, int algo,
                        hipStream_t stream);
+
+// Scratch bytes with which launch_conv may run a layer on the matrix cores (0:
+// it never does).
+size_t conv_workspace_bytes(int dtype, int cout, int cin);
+// Whether it does for this call, given the scratch (host only).
+bool conv_mfma_takes(const PatTable& tab, const ConvArgs& a);
 
 // The launch configuration launch_conv would use (host only, no device work).
 struct ConvForm {

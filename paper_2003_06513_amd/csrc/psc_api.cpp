@@ -324,7 +324,8 @@ static psc::ConvArgs conv_args(const psc_layer* L, int32_t act_dtype, const void
 
 static psc_status conv_common(const psc_layer* L, const psc_packed* pk, int32_t act_dtype, const void* d_x,
                               int32_t n, int32_t h, int32_t w, const void* d_bias, int32_t relu, void* d_y,
-                              int32_t algo, int pool, int32_t stride, void* stream) {
+                              int32_t algo, int pool, int32_t stride, void* stream, void* d_ws = nullptr,
+                              size_t ws_bytes = 0) {
     if (psc_status s = check_conv_shape(L, act_dtype, n, h, w, algo, pool, stride)) return s;
     if (psc_status s = check_packed(L, pk)) return s;
     const int64_t plane = int64_t(h) * w;
@@ -340,7 +341,11 @@ static psc_status conv_common(const psc_layer* L, const psc_packed* pk, int32_t 
     const psc::PatTable t = table_of(L);
     const psc::PackedView v{pk->filter_perm, pk->filter_ptr, pk->seg_ptr,
                             pk->cin_idx,     pk->pat_id,     pk->values};
-    const psc::ConvArgs a = conv_args(L, act_dtype, d_x, n, h, w, d_bias, relu, d_y, pool, stride);
+    if (reinterpret_cast<uintptr_t>(d_ws) & 255u)
+        return fail(PSC_ERR_WORKSPACE, "workspace must be 256-byte aligned");
+    psc::ConvArgs a = conv_args(L, act_dtype, d_x, n, h, w, d_bias, relu, d_y, pool, stride);
+    a.ws = d_ws;
+    a.ws_bytes = ws_bytes;
     return device_status(psc::launch_conv(t, v, a, algo, as_stream(stream)), "psc_conv3x3_fwd launch");
 }
 
@@ -380,6 +385,30 @@ psc_status psc_conv3x3_fwd_strided(const psc_layer* L, const psc_packed* pk, int
                                    const void* d_x, int32_t n, int32_t h, int32_t w, const void* d_bias,
                                    int32_t relu, void* d_y, int32_t stride, int32_t algo, void* stream) {
     return conv_common(L, pk, act_dtype, d_x, n, h, w, d_bias, relu, d_y, algo, 0, stride, stream);
+}
+
+psc_status psc_conv3x3_workspace(const psc_layer* L, size_t* bytes) {
+    if (psc_status s = check_layer(L, true)) return s;
+    if (!bytes) return fail(PSC_ERR_ARG, "bytes is NULL");
+    *bytes = psc::conv_workspace_bytes(L->wdtype, L->cout, L->cin);
+    return ok();
+}
+
+psc_status psc_conv3x3_on_matrix_cores(const psc_layer* L, int32_t act_dtype, int32_t n, int32_t h, int32_t w,
+                                       int32_t pool, int32_t stride, int32_t* out) {
+    if (psc_status s = check_conv_shape(L, act_dtype, n, h, w, 0, pool != 0, stride)) return s;
+    if (!out) return fail(PSC_ERR_ARG, "out is NULL");
+    const psc::ConvArgs a = conv_args(L, act_dtype, nullptr, n, h, w, nullptr, 0, nullptr, pool != 0, stride);
+    *out = n > 0 && psc::conv_mfma_takes(table_of(L), a);
+    return ok();
+}
+
+psc_status psc_conv3x3_fwd_ws(const psc_layer* L, const psc_packed* pk, int32_t act_dtype, const void* d_x,
+                              int32_t n, int32_t h, int32_t w, const void* d_bias, int32_t relu, void* d_y,
+                              int32_t pool, int32_t stride, int32_t algo, void* d_ws, size_t ws_bytes,
+                              void* stream) {
+    return conv_common(L, pk, act_dtype, d_x, n, h, w, d_bias, relu, d_y, algo, pool != 0, stride, stream, d_ws,
+                       ws_bytes);
 }
 
 psc_status psc_transpose_layer(const psc_layer* L, psc_layer* out) {
