@@ -6,6 +6,9 @@
 namespace psc {
 
 enum : int { DT_F32 = 0, DT_F16 = 1 };
+
+// A constant as an argument.
+template <int V> struct IntC { static constexpr int value = V; };
 constexpr int kMaxPatterns = 126;
 
 // The pattern library as a kernel argument (Sec. 3.2: m masks of 4 kept

@@ -88,7 +88,7 @@ bool conv_rows_takes(const PatTable& tab, const ConvArgs& a);
 hipError_t launch_transpose_prep(int dtype, int cout, int cin, const void* w, const uint8_t* pat,
                                  const uint8_t* keep, void* wt, uint8_t* pat_t, uint8_t* keep_t,
                                  hipStream_t stream);
-size_t wgrad_workspace_bytes(int n, int cin, int cout, int h, int w, int64_t nk, bool dense);
+size_t wgrad_workspace_bytes(int n, int cin, int cout, int h, int w, int64_t nk, bool dense, int dtype);
 // Measurement probe: blocks x 256 lanes, each 8 x iters fp32 FMAs; out [blocks*256].
 hipError_t launch_probe_fma(int blocks, int iters, float* out, hipStream_t stream);
 // Measurement probe: blocks x 4 waves, each 4 chains of iters fp32 MFMA 16x16x4; out [blocks*256].
@@ -106,21 +106,30 @@ hipError_t launch_admm_residual(const float* z, const float* t, int64_t numel, f
 hipError_t launch_dense_wgrad(const float* x, const float* g, int n, int cin, int h, int w, int cout, float* dw,
                               float* db, void* ws, hipStream_t stream);
 // The dense weight gradient on the matrix cores (layers of at least 16 input
-// channels): blocks of 64 filters x 16 channels, the 4x16 pixel tiles split
-// over KS blocks with KS partial-sum slots in the workspace.
+// channels): blocks of 32 WT filters x 32 WT channels, tiles of RT rows x GT
+// groups of 8 columns split over KS blocks with KS partial-sum slots in the
+// workspace.
 struct DenseWPlan {
+    int WT;
     int fb, cb;             // filter and channel blocks
-    int tiles_w, tiles_img; // pixel tiles per image row of tiles, per image
-    int64_t tiles;          // pixel tiles in all
+    int RT, GT;             // rows and column groups of a tile
+    int DU;                 // units of a tile's gradient, padded to whole steps
+    int U;                  // staged groups of an input row: GT, or GT + 2 with halo groups
+    int gtiles;             // tiles of a row
+    int64_t tiles;          // tiles in all
     int KS;                 // blocks the tiles are split over
+    int lds;                // bytes
+    uint32_t gt_m, u_m, h_m;    // 2^32 / GT, U and H + 1
 };
-bool dense_wgrad_mfma_plan(int n, int cin, int cout, int h, int w, DenseWPlan* p);
+bool dense_wgrad_mfma_plan(int n, int cin, int cout, int h, int w, int dtype, DenseWPlan* p);
 size_t dense_wgrad_mfma_workspace(const DenseWPlan& p, int cin, int cout);
 hipError_t launch_dense_wgrad_mfma(const DenseWPlan& p, int dtype, const void* x, const void* g, int n, int cin,
-                                   int h, int w, int cout, float* dst, hipStream_t stream);
-// The masked gradient of the stored kernels taken from a dense dw [cout][cin][9].
-hipError_t launch_gather_masked(const PatTable& tab, const PackedView& pk, int cout, int cin, const float* dw,
-                                float* dv, hipStream_t stream);
+                                   int h, int w, int cout, float* slots, hipStream_t stream);
+// dw [cout][cin][9], and the masked gradient of the stored kernels, from the
+// KS slots [cout][9][cin].
+hipError_t launch_sum_slots(const DenseWPlan& p, const float* part, int cin, int cout, float* dw, hipStream_t stream);
+hipError_t launch_gather_masked(const PatTable& tab, const PackedView& pk, int cout, int cin, int64_t keep,
+                                const float* part, int KS, float* dv, hipStream_t stream);
 hipError_t launch_admm_primal(float* w, const float* dw, const float* a, const float* d, int64_t nw, float* b,
                               const float* db, int cout, float lr, float rho, float* v, hipStream_t stream);
 hipError_t launch_admm_dual(const PatTable& tab, const float* v, const uint8_t* pat, const uint8_t* keep, int64_t nk,

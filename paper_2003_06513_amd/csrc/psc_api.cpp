@@ -450,7 +450,7 @@ psc_status psc_conv3x3_bwd_weight_workspace(const psc_layer* L, int32_t act_dtyp
                                             size_t* bytes) {
     if (psc_status s = check_conv_shape(L, act_dtype, n, h, w, 0, 0, 1)) return s;
     if (!bytes) return fail(PSC_ERR_ARG, "bytes is NULL");
-    *bytes = psc::wgrad_workspace_bytes(n, L->cin, L->cout, h, w, L->keep, false);
+    *bytes = psc::wgrad_workspace_bytes(n, L->cin, L->cout, h, w, L->keep, false, act_dtype);
     return ok();
 }
 
@@ -459,7 +459,7 @@ psc_status psc_conv3x3_bwd_weight(const psc_layer* L, const psc_packed* pk, int3
                                   float* d_dbias, void* d_ws, size_t ws_bytes, void* stream) {
     if (psc_status s = check_conv_shape(L, act_dtype, n, h, w, 0, 0, 1)) return s;
     if (psc_status s = check_packed(L, pk)) return s;
-    const size_t need = psc::wgrad_workspace_bytes(n, L->cin, L->cout, h, w, L->keep, false);
+    const size_t need = psc::wgrad_workspace_bytes(n, L->cin, L->cout, h, w, L->keep, false, act_dtype);
     if (need && (!d_ws || ws_bytes < need))
         return fail(PSC_ERR_WORKSPACE, "bwd weight needs %zu workspace bytes, got %zu", need, ws_bytes);
     if (n == 0) return ok();
@@ -503,7 +503,7 @@ psc_status psc_dense3x3_bwd_weight_workspace(int32_t n, int32_t cin, int32_t h, 
                                              size_t* bytes) {
     if (psc_status s = check_dense_wgrad_shape(n, cin, h, w, cout)) return s;
     if (!bytes) return fail(PSC_ERR_ARG, "bytes is NULL");
-    *bytes = psc::wgrad_workspace_bytes(n, cin, cout, h, w, int64_t(cout) * cin, true);
+    *bytes = psc::wgrad_workspace_bytes(n, cin, cout, h, w, int64_t(cout) * cin, true, PSC_F32);
     return ok();
 }
 
@@ -513,7 +513,7 @@ psc_status psc_dense3x3_bwd_weight(const float* d_x, const float* d_g, int32_t n
     if (psc_status s = check_dense_wgrad_shape(n, cin, h, w, cout)) return s;
     if (!d_dw) return fail(PSC_ERR_ARG, "d_dw must be non-NULL");
     if (n > 0 && (!d_x || !d_g)) return fail(PSC_ERR_ARG, "d_x and d_g must be non-NULL");
-    const size_t need = psc::wgrad_workspace_bytes(n, cin, cout, h, w, int64_t(cout) * cin, true);
+    const size_t need = psc::wgrad_workspace_bytes(n, cin, cout, h, w, int64_t(cout) * cin, true, PSC_F32);
     if (need && (!d_ws || ws_bytes < need))
         return fail(PSC_ERR_WORKSPACE, "dense bwd weight needs %zu workspace bytes, got %zu", need, ws_bytes);
     if (n == 0) return ok();

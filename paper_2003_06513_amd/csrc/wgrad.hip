@@ -56,23 +56,18 @@ extern template hipError_t launch_wgrad<DT_F16, 4, 4, 0, false, true>(dim3, cons
 namespace {
 using namespace wg;
 
-// out[e] = sum over shares s (in order) of part[s][e]; the loads of four
-// shares are issued together, the adds keep the share order.
+// out[e] = sum over shares s of part[s][e], in a fixed order: four chains
+// (s % 4), then their sum.
 __global__ __launch_bounds__(256) void k_wgrad_reduce(const float* __restrict__ part, int KS, int64_t n,
                                                       float* __restrict__ out) {
     for (int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x; e < n; e += int64_t(gridDim.x) * 256) {
-        float v = part[e];
-        int s = 1;
-        for (; s + 4 <= KS; s += 4) {
-            const float a = part[int64_t(s) * n + e], b = part[int64_t(s + 1) * n + e];
-            const float c = part[int64_t(s + 2) * n + e], d = part[int64_t(s + 3) * n + e];
-            v += a;
-            v += b;
-            v += c;
-            v += d;
-        }
-        for (; s < KS; ++s) v += part[int64_t(s) * n + e];
-        out[e] = v;
+        float a[4] = {0.f, 0.f, 0.f, 0.f};
+        int s = 0;
+        for (; s + 4 <= KS; s += 4)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) a[t] += part[int64_t(s + t) * n + e];
+        for (; s < KS; ++s) a[0] += part[int64_t(s) * n + e];
+        out[e] = (a[0] + a[1]) + (a[2] + a[3]);
     }
 }
 
@@ -293,28 +288,28 @@ static size_t wgrad_part_bytes(const WGeo& g, int64_t nk, bool dense) {
     return g.KS > 1 && g.n > 0 ? size_t(g.KS) * size_t(nk) * (dense ? 9 : 4) * sizeof(float) : 0;
 }
 
-// The masked gradient of a batch-1 layer of at least 16 input channels is
-// taken from the dense one on the matrix cores: there the masked kernels are
-// bound by load latency, and the dense GEMM over one image's pixels was
-// measured faster on the VGG-16 and ResNet-50 layers although it does
-// 9 / (4 keep) times the work.  Larger batches keep the masked kernels.
-static bool masked_via_dense(int n, int cin, int cout, int h, int w, DenseWPlan* dp) {
-    return n == 1 && dense_wgrad_mfma_plan(n, cin, cout, h, w, dp);
+// Whether the masked gradient of a layer is taken from the dense one on the
+// matrix cores.  At batch 1 the masked kernels are bound by load latency
+// (fp16 512 @ 14x14: 41 us, dense 31; fp32 256 @ 56x56: 72, dense 59).  At
+// larger batches their time falls with the kernels kept and the dense one's
+// does not: at 40 % kept and full groups of 8 columns it takes about half in
+// fp16 (64 @ 32x32 b256 304 -> 105 us) and 0.6 in fp32 (256 @ 8x8 b256
+// 254 -> 157), which puts the lines at 18 and 25 % of the kernels.
+static bool masked_via_dense(int n, int cin, int cout, int h, int w, int64_t keep, int dtype, DenseWPlan* dp) {
+    if (!dense_wgrad_mfma_plan(n, cin, cout, h, w, dtype, dp)) return false;
+    const int64_t cols = (w + 7) / 8 * 8, line = dtype == DT_F16 ? 18 : 25;
+    return n == 1 || 100 * keep * w >= line * cin * cout * cols;
 }
 
-size_t wgrad_workspace_bytes(int n, int cin, int cout, int h, int w, int64_t nk, bool dense) {
+size_t wgrad_workspace_bytes(int n, int cin, int cout, int h, int w, int64_t nk, bool dense, int dtype) {
     if (n <= 0) return 0;
     const int P = bias_parts(n, h * w);
     const size_t bias_bytes = P > 1 ? size_t(P) * size_t(cout) * sizeof(float) : 0;
     DenseWPlan dp;
-    if (dense && dense_wgrad_mfma_plan(n, cin, cout, h, w, &dp)) return dense_wgrad_mfma_workspace(dp, cin, cout) + bias_bytes;
-    // the masked route through the dense gradient needs the dense dW as well
-    if (!dense && masked_via_dense(n, cin, cout, h, w, &dp)) {
-        const WGeo g = plan(n, cin, cout, h, w, nk, false, nullptr, DT_F32);
-        const size_t via = dense_wgrad_mfma_workspace(dp, cin, cout) + size_t(cout) * size_t(cin) * 9 * sizeof(float);
-        const size_t direct = wgrad_part_bytes(g, nk, false);
-        return (via > direct ? via : direct) + bias_bytes;
-    }
+    if (dense && dense_wgrad_mfma_plan(n, cin, cout, h, w, dtype, &dp))
+        return dense_wgrad_mfma_workspace(dp, cin, cout) + bias_bytes;
+    if (!dense && nk > 0 && masked_via_dense(n, cin, cout, h, w, nk, dtype, &dp))
+        return dense_wgrad_mfma_workspace(dp, cin, cout) + bias_bytes;
     const WGeo g = plan(n, cin, cout, h, w, nk, dense, nullptr, DT_F32);
     return wgrad_part_bytes(g, nk, dense) + bias_bytes;
 }
@@ -322,29 +317,17 @@ size_t wgrad_workspace_bytes(int n, int cin, int cout, int h, int w, int64_t nk,
 hipError_t launch_bwd_weight(const PatTable& tab, const PackedView& pk, int dtype, int n, int cin, int h, int w,
                              int cout, int64_t keep, const void* x, const void* dy, float* dv, float* db, void* ws,
                              hipStream_t stream) {
-    const WGeo g = plan(n, cin, cout, h, w, keep, false, &tab, dtype);
     DenseWPlan dp;
     hipError_t e;
-    size_t part_bytes = wgrad_part_bytes(g, keep, false);
-    if (keep > 0 && masked_via_dense(n, cin, cout, h, w, &dp)) {
-        // workspace: the matrix-core partial sums, then the dense dW, then
-        // (after the larger of this and the masked kernels' partial sums,
-        // as sized by wgrad_workspace_bytes) the bias parts
-        const size_t slots = dense_wgrad_mfma_workspace(dp, cin, cout);
-        float* dense_dw = reinterpret_cast<float*>(static_cast<char*>(ws) + slots);
-        e = launch_dense_wgrad_mfma(dp, dtype, x, dy, n, cin, h, w, cout, dp.KS > 1 ? static_cast<float*>(ws) : dense_dw,
-                                    stream);
-        if (e == hipSuccess && dp.KS > 1) {
-            const int64_t ne = int64_t(cout) * cin * 9;
-            const int64_t gb = (ne + 255) / 256;
-            hipLaunchKernelGGL(k_wgrad_reduce, dim3(unsigned(gb > 8192 ? 8192 : gb)), dim3(256), 0, stream,
-                               static_cast<const float*>(ws), dp.KS, ne, dense_dw);
-            e = hipGetLastError();
-        }
-        if (e == hipSuccess) e = launch_gather_masked(tab, pk, cout, cin, dense_dw, dv, stream);
-        const size_t via = slots + size_t(cout) * size_t(cin) * 9 * sizeof(float);
-        part_bytes = via > part_bytes ? via : part_bytes;
+    size_t part_bytes;
+    if (keep > 0 && masked_via_dense(n, cin, cout, h, w, keep, dtype, &dp)) {
+        part_bytes = dense_wgrad_mfma_workspace(dp, cin, cout);
+        float* const part = static_cast<float*>(ws);
+        e = launch_dense_wgrad_mfma(dp, dtype, x, dy, n, cin, h, w, cout, part, stream);
+        if (e == hipSuccess) e = launch_gather_masked(tab, pk, cout, cin, keep, part, dp.KS, dv, stream);
     } else {
+        const WGeo g = plan(n, cin, cout, h, w, keep, false, &tab, dtype);
+        part_bytes = wgrad_part_bytes(g, keep, false);
         e = dtype == DT_F16 ? run<DT_F16, 4>(g, x, dy, pk.filter_perm, pk.seg_ptr, pk.cin_idx, dv, ws, stream)
                             : run<DT_F32, 4>(g, x, dy, pk.filter_perm, pk.seg_ptr, pk.cin_idx, dv, ws, stream);
     }
@@ -359,18 +342,12 @@ hipError_t launch_dense_wgrad(const float* x, const float* g_, int n, int cin, i
     hipError_t e;
     size_t part_bytes;
     DenseWPlan dp;
-    if (dense_wgrad_mfma_plan(n, cin, cout, h, w, &dp)) {
-        // matrix cores: KS slots of partial sums, added in slot order
+    if (dense_wgrad_mfma_plan(n, cin, cout, h, w, DT_F32, &dp)) {
+        // matrix cores: KS slots of partial sums, then their sum
         part_bytes = dense_wgrad_mfma_workspace(dp, cin, cout);
-        e = launch_dense_wgrad_mfma(dp, DT_F32, x, g_, n, cin, h, w, cout, dp.KS > 1 ? static_cast<float*>(ws) : dw,
-                                    stream);
-        if (e == hipSuccess && dp.KS > 1) {
-            const int64_t ne = int64_t(cout) * cin * 9;
-            const int64_t gb = (ne + 255) / 256;
-            hipLaunchKernelGGL(k_wgrad_reduce, dim3(unsigned(gb > 8192 ? 8192 : gb)), dim3(256), 0, stream,
-                               static_cast<const float*>(ws), dp.KS, ne, dw);
-            e = hipGetLastError();
-        }
+        float* const part = static_cast<float*>(ws);
+        e = launch_dense_wgrad_mfma(dp, DT_F32, x, g_, n, cin, h, w, cout, part, stream);
+        if (e == hipSuccess) e = launch_sum_slots(dp, part, cin, cout, dw, stream);
     } else {
         const WGeo g = plan(n, cin, cout, h, w, int64_t(cout) * cin, true, nullptr, DT_F32);
         part_bytes = wgrad_part_bytes(g, int64_t(cout) * cin, true);

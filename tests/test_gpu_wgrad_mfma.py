@@ -1,0 +1,120 @@
+"""The matrix-core weight gradient at the sizes where its tiles can go wrong,
+against a float64 sum on the CPU: dense (fp32, from three bf16 parts) and
+masked (fp16 and fp32).  The bound per entry is gamma_n times the sum of the
+absolute products, n the number of pixels (each of the n products is exact or
+within 2^-26, each addition rounds once)."""
+import numpy as np
+import pytest
+
+from paper_2003_06513_amd import binding as B
+from synthetic import inputs
+from gpu_cases import dev, gamma, note, torch_mod
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    B.lib()
+
+
+def _wgrad(x, g):
+    """float64 dW [cout][cin][9] by the definition."""
+    n, c, h, w = x.shape
+    p = np.zeros((n, c, h + 2, w + 2))
+    p[:, :, 1:-1, 1:-1] = x
+    g2 = g.astype(np.float64).transpose(1, 0, 2, 3).reshape(g.shape[1], -1)
+    out = np.empty((g.shape[1], c, 9))
+    for q in range(9):
+        t = p[:, :, q // 3:q // 3 + h, q % 3:q % 3 + w].transpose(1, 0, 2, 3).reshape(c, -1)
+        out[:, :, q] = g2 @ t.T
+    return out
+
+
+# n, cin, cout, h, w: one to several groups of 8 columns with every remainder,
+# rows split over tiles with halo groups, images inside and across tiles,
+# ragged filters and channels, 32- and 64-wide blocks, one and many slots
+SHAPES = [(1, 16, 1, 1, 1), (3, 17, 5, 2, 3), (5, 33, 40, 4, 4), (2, 16, 33, 7, 7), (4, 31, 70, 8, 8),
+          (2, 40, 36, 9, 13), (1, 20, 65, 5, 16), (2, 16, 32, 6, 31), (1, 18, 34, 3, 61), (1, 32, 16, 5, 130),
+          (1, 16, 20, 2, 300), (40, 16, 16, 4, 5), (9, 48, 24, 16, 15), (64, 512, 512, 4, 8), (2, 16, 16, 70, 9)]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=["x".join(map(str, s)) for s in SHAPES])
+def test_dense_fp32(shape):
+    torch = torch_mod()
+    n, cin, cout, h, w = shape
+    x, g = inputs.normal_activations(3, (n, cin, h, w)), inputs.normal_activations(4, (n, cout, h, w))
+    dw, db = torch.empty((cout, cin, 3, 3), device="cuda"), torch.empty(cout, device="cuda")
+    note("dense wgrad %s" % (shape,))
+    ws = B.dense3x3_bwd_weight(dev(x), dev(g), dw, db)
+    first = dw.clone()
+    if ws is not None:
+        ws.fill_(255)
+    B.dense3x3_bwd_weight(dev(x), dev(g), dw, db, ws=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(first, dw)
+    err = np.abs(dw.cpu().numpy().reshape(cout, cin, 9) - _wgrad(x, g))
+    bound = gamma(6 * n * h * w) * _wgrad(np.abs(x), np.abs(g)) + 1e-37
+    assert (err <= bound).all(), float((err / bound).max())
+    ref = g.astype(np.float64).sum((0, 2, 3))
+    assert np.abs(db.cpu().numpy() - ref).max() <= gamma(n * h * w) * np.abs(g).sum((0, 2, 3)).max() + 1e-37
+
+
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+@pytest.mark.parametrize("shape", SHAPES[2:10], ids=["x".join(map(str, s)) for s in SHAPES[2:10]])
+def test_masked(shape, dtype):
+    torch = torch_mod()
+    n, cin, cout, h, w = shape
+    x = inputs.normal_activations(5, (n, cin, h, w), dtype)
+    g = inputs.normal_activations(6, (n, cout, h, w), dtype)
+    wt = inputs.he_weights(7, cout, cin, dtype)
+    masks = B.select_library(wt, 8)
+    keep = inputs.keep_after_drop(cout * cin, 20)
+    prep = B.prepare(dev(wt), masks, keep)
+    dv = torch.empty(4 * keep, device="cuda")
+    note("masked wgrad %s %s" % (shape, np.dtype(dtype).name))
+    B.conv3x3_bwd_weight(prep.layer, prep.packed, dev(x), dev(g), dv)
+    pk = prep.packed.to_host()
+    pos = np.repeat(np.arange(cout), np.diff(pk["filter_ptr"]))
+    bits = np.array([[b for b in range(9) if (int(c) >> b) & 1] for c in masks])[pk["pat_id"]]
+    at = (pk["filter_perm"][pos][:, None], pk["cin_idx"][:, None], bits)
+    err = np.abs(dv.cpu().numpy().reshape(-1, 4) - _wgrad(x, g)[at])
+    bound = gamma(6 * n * h * w) * _wgrad(np.abs(x), np.abs(g))[at] + 1e-37
+    assert (err <= bound).all(), float((err / bound).max())
+
+
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** -122])
+def test_values_that_bf16_parts_cannot_hold(scale):
+    """Infinities and NaNs reach the entries that read them and no others
+    (the zero columns beside the image must not make a NaN of an infinity);
+    values near the smallest normal number keep their precision."""
+    torch = torch_mod()
+    n, cin, cout, h, w = 3, 40, 33, 6, 13
+    x, g = inputs.normal_activations(3, (n, cin, h, w)), inputs.normal_activations(4, (n, cout, h, w))
+    g *= np.float32(scale)
+    if scale == 1.0:
+        x[0, 1, 0, 0], x[1, 2, 5, 12], x[2, 3, 2, 12], x[0, 5, 3, 3] = np.inf, -np.inf, np.nan, 3.4e38
+        g[1, 4, 5, 0] = np.inf
+    dw = torch.empty((cout, cin, 3, 3), device="cuda")
+    note("wgrad non-finite, scale %g" % scale)
+    B.dense3x3_bwd_weight(dev(x), dev(g), dw)
+    got = dw.cpu().numpy().reshape(cout, cin, 9).astype(np.float64)
+    want = np.empty_like(got)
+    with np.errstate(all="ignore"):
+        for q in range(9):
+            r, s = q // 3 - 1, q % 3 - 1
+            i0, i1, j0, j1 = max(0, -r), min(h, h - r), max(0, -s), min(w, w - s)
+            xs = x[:, :, i0 + r:i1 + r, j0 + s:j1 + s].astype(np.float64)
+            gs = g[:, :, i0:i1, j0:j1].astype(np.float64)
+            want[:, :, q] = (gs[:, :, None] * xs[:, None]).sum((0, 3, 4))
+    # 3.4e38 times a few may pass the largest number: those entries may differ in kind
+    big = np.zeros(got.shape, bool)
+    big[:, 5] = scale == 1.0
+    assert np.array_equal(np.isnan(got)[~big], np.isnan(want)[~big])
+    assert np.array_equal(np.isinf(got)[~big], np.isinf(want)[~big])
+    ok = np.isfinite(want) & ~big
+    mag = _wgrad(np.where(np.isfinite(x), np.abs(x), 0), np.where(np.isfinite(g), np.abs(g), 0))
+    assert (np.abs(got[ok] - want[ok]) <= gamma(6 * n * h * w) * mag[ok] + 300 * 2.0 ** -149).all()
