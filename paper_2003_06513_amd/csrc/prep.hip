@@ -223,74 +223,263 @@ __global__ __launch_bounds__(256) void k_sel_mark(const uint64_t* __restrict__ k
     }
 }
 
-// The whole selection in one workgroup of 1024 threads, for layers of at
-// most kSelOneBlockMax kernels, where the passes above would be bound by
-// their 19 launches: the same 8 radix passes (histogram of the keys that
-// match the digits found so far, then the same digit), then the same
-// index-ordered rank of the keys equal to the threshold
-// -- each thread owns a contiguous run of indices -- so the keep mask is the
-// same bit for bit.
-constexpr int64_t kSelOneBlockMax = 65536;
+// ---- Selection without the fixed 8 passes (layers of at most kSelFastMax
+// kernels).  A block narrows a set of candidate keys to the threshold T: each
+// round takes the bits that all candidates share as decided, histograms the
+// next 11, and keeps the bin in which the count from the top reaches r.  It
+// ends as soon as a bin is kept whole (T is then the bin's lower end) or all
+// candidates are equal; random energies take two or three rounds.  Among the
+// keys equal to T the lowest indices are kept, up to an index `cut`, so the
+// keep mask is the same bit for bit.
+constexpr int kSelBins = 2048;
+constexpr int64_t kSelOneBlockMax = 16384, kSelFastMax = int64_t(1) << 20;
 
+struct SelCut {
+    uint64_t T;      // threshold
+    int64_t cut;     // keep key > T, and key == T up to this index
+};
+
+struct SelShared {
+    uint32_t hist[kSelBins];
+    uint64_t w_and[16], w_or[16];
+    uint32_t part[1024];
+    uint32_t wsum[16];
+    int digit;
+    int64_t above, cut;
+};
+
+// The largest bin d with S(d) >= r, S(d) the count of bins d and up, and
+// S(d + 1), from `bins` counters (a multiple of 1024; S(0) >= r).  Every
+// thread of a 1024-thread block calls it.
+__device__ __forceinline__ void sel_bin(const uint32_t* hist, int bins, int64_t r, SelShared& sh) {
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, per = bins / 1024;
+    // thread t owns the bins from the top down: per * t .. per * t + per - 1
+    uint32_t own = 0;
+    for (int j = 0; j < per; ++j) own += hist[bins - 1 - per * t - j];
+    uint32_t inc = own;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t v = __shfl_up(inc, off);
+        if (lane >= off) inc += v;
+    }
+    if (lane == 63) sh.wsum[wave] = inc;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) inc += sh.wsum[w];
+    const uint32_t before = inc - own;
+    if (int64_t(before) < r && int64_t(inc) >= r) {      // one thread
+        int64_t run = before;
+        int d = bins - 1 - per * t;
+        while (run + int64_t(hist[d]) < r) run += hist[d--];
+        sh.digit = d;
+        sh.above = run;
+    }
+    __syncthreads();
+}
+
+// T and cut of the r largest of n candidates (those that match the decided
+// bits `mask` of `prefix`; 1 <= r <= their number).  key(i) and index(i) name
+// the i-th key and its index; `ordered`: index(i) ascends with i.  All 1024
+// threads call it.
+template <typename Key, typename Index>
+__device__ SelCut sel_narrow(Key key, Index index, bool ordered, int64_t n, int64_t r, uint64_t prefix, uint64_t mask,
+                             SelShared& sh) {
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    uint64_t T = 0;
+    bool all = false;                                    // every candidate that is left is kept
+    for (;;) {
+        uint64_t va = ~uint64_t(0), vo = 0;
+        for (int64_t i = t; i < n; i += 1024) {
+            const uint64_t k = key(i);
+            if ((k & mask) == prefix) va &= k, vo |= k;
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            va &= uint64_t(__shfl_xor((unsigned long long)va, off));
+            vo |= uint64_t(__shfl_xor((unsigned long long)vo, off));
+        }
+        if (lane == 0) sh.w_and[wave] = va, sh.w_or[wave] = vo;
+        for (int b = t; b < kSelBins; b += 1024) sh.hist[b] = 0;
+        __syncthreads();
+        for (int w = 0; w < 16; ++w) va &= sh.w_and[w], vo |= sh.w_or[w];
+        const uint64_t diff = va ^ vo;
+        if (diff == 0) {
+            T = va;
+            break;
+        }
+        const int hb = 63 - __clzll((long long)diff), shift = hb > 10 ? hb - 10 : 0;
+        const uint64_t low = (uint64_t(2) << hb) - 1;    // all ones for hb = 63
+        mask = ~low;
+        prefix = va & mask;
+        for (int64_t i = t; i < n; i += 1024) {
+            const uint64_t k = key(i);
+            if ((k & mask) == prefix) atomicAdd(&sh.hist[(k & low) >> shift], 1u);
+        }
+        __syncthreads();
+        sel_bin(sh.hist, kSelBins, r, sh);
+        const int d = sh.digit;
+        r -= sh.above;
+        prefix |= uint64_t(d) << shift;
+        mask = shift ? ~((uint64_t(1) << shift) - 1) : ~uint64_t(0);
+        all = int64_t(sh.hist[d]) == r;
+        __syncthreads();
+        if (all || shift == 0) {
+            T = prefix;
+            break;
+        }
+    }
+    if (all) return SelCut{T, INT64_MAX};
+    // the r-th lowest index of the keys equal to T
+    if (t == 0) sh.cut = INT64_MAX;
+    __syncthreads();
+    if (ordered) {
+        const int64_t per = (n + 1023) / 1024, beg = min<int64_t>(n, t * per), end = min<int64_t>(n, beg + per);
+        uint32_t c = 0;
+        for (int64_t i = beg; i < end; ++i) c += key(i) == T;
+        sh.part[t] = c;
+        __syncthreads();
+        for (int off = 1; off < 1024; off <<= 1) {
+            const uint32_t v = t >= off ? sh.part[t - off] : 0u;
+            __syncthreads();
+            sh.part[t] += v;
+            __syncthreads();
+        }
+        int64_t rank = int64_t(sh.part[t]) - c;
+        if (rank < r && rank + c >= r)
+            for (int64_t i = beg; i < end; ++i)
+                if (key(i) == T && ++rank == r) sh.cut = index(i);
+    } else {
+        for (int64_t i = t; i < n; i += 1024) {
+            if (key(i) != T) continue;
+            const int64_t at = index(i);
+            int64_t rank = 0;
+            for (int64_t j = 0; j < n; ++j) rank += key(j) == T && index(j) < at;
+            if (rank == r - 1) sh.cut = at;
+        }
+    }
+    __syncthreads();
+    return SelCut{T, sh.cut};
+}
+
+// The whole selection in one workgroup (at most kSelOneBlockMax keys, up to
+// 16 of them in each thread's registers).
+template <int KPT>
 __global__ __launch_bounds__(1024) void k_sel_one(const uint64_t* __restrict__ keys, int64_t n, int64_t keep,
                                                   uint8_t* __restrict__ out) {
-    __shared__ uint32_t hist[256];
-    __shared__ uint32_t part[1024];
-    __shared__ uint64_t sfx[257];
-    __shared__ uint64_t s_prefix, s_mask;
-    __shared__ int64_t s_rem;
-    __shared__ int s_d;
-    const int t = threadIdx.x;
-    if (t == 0) {
-        s_prefix = 0;
-        s_mask = 0;
-        s_rem = keep;
+    __shared__ SelShared sh;
+    uint64_t kv[KPT];
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) {
+        const int64_t i = threadIdx.x + 1024 * j;
+        kv[j] = i < n ? keys[i] : 0;
     }
-    for (int shift = 56; shift >= 0; shift -= 8) {
-        if (t < 256) hist[t] = 0;
-        __syncthreads();
-        const uint64_t prefix = s_prefix, mask = s_mask;
-        for (int64_t i = t; i < n; i += 1024) {
-            const uint64_t key = keys[i];
-            if ((key & mask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1u);
-        }
-        __syncthreads();
-        const int64_t r = s_rem;
-        int64_t above;
-        const int d = sel_digit(hist, r, sfx, &s_d, &above);
-        __syncthreads();   // every thread has read s_rem, s_d and sfx
-        if (t == 0) {
-            s_rem = r - above;
-            s_prefix = prefix | (uint64_t(d) << shift);
-            s_mask = mask | (uint64_t(255) << shift);
-        }
+    // key(i) for i = threadIdx.x + 1024 j comes from the registers; ties are
+    // ranked over contiguous runs, from memory
+    const SelCut c = sel_narrow(
+        [&](int64_t i) {
+            uint64_t k = 0;
+            if ((i & 1023) == int64_t(threadIdx.x)) {
+#pragma unroll
+                for (int j = 0; j < KPT; ++j) k = (i >> 10) == j ? kv[j] : k;
+                return k;
+            }
+            return keys[i];
+        },
+        [](int64_t i) { return i; }, true, n, keep, 0, 0, sh);
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) {
+        const int64_t i = threadIdx.x + 1024 * j;
+        if (i < n) out[i] = kv[j] > c.T || (kv[j] == c.T && i <= c.cut);
+    }
+}
+
+// More keys: two histograms of 12 bits (sign and exponent, then the top of
+// the mantissa) over the whole grid, the keys of the bin that is left in a
+// list, T and cut from the list in one block, then the mask: 6 launches.  Each
+// block takes the digit of the pass before from its histogram.  A list that
+// overflows (thousands of equal leading bits) makes the one block go over all
+// the keys instead.
+constexpr int kSelWide = 4096, kSelList = 2560;
+struct SelWide {
+    uint32_t hist[2][kSelWide];
+    uint32_t count;
+    uint32_t pad[63];
+    SelCut cut;
+    uint64_t pad2[30];
+    uint64_t key[kSelList];
+    uint32_t index[kSelList];
+};
+static_assert(sizeof(SelWide) <= 64 * 1024, "the scratch of psc_select_noalloc");
+
+__global__ __launch_bounds__(1024) void k_selw_clear(SelWide* __restrict__ s) {
+    for (int i = threadIdx.x; i < 2 * kSelWide; i += 1024) (&s->hist[0][0])[i] = 0;
+    if (threadIdx.x == 0) s->count = 0;
+}
+
+// Pass 0 or 1, or (pass 2) the list of the keys that match both digits.
+template <int PASS>
+__global__ __launch_bounds__(1024) void k_selw_pass(const uint64_t* __restrict__ keys, int64_t n, int64_t keep,
+                                                    SelWide* __restrict__ s) {
+    __shared__ SelShared sh;
+    __shared__ uint32_t lh[PASS < 2 ? kSelWide : 1];
+    int64_t r = keep;
+    uint64_t prefix = 0;
+#pragma unroll
+    for (int p = 0; p < PASS; ++p) {
+        sel_bin(s->hist[p], kSelWide, r, sh);
+        r -= sh.above;
+        prefix = prefix << 12 | uint64_t(sh.digit);
         __syncthreads();
     }
-    const uint64_t T = s_prefix;
-    const int64_t r = s_rem;
-    const int64_t per = (n + 1023) / 1024;
-    const int64_t beg = min<int64_t>(n, t * per), end = min<int64_t>(n, beg + per);
-    uint32_t c = 0;
-    for (int64_t i = beg; i < end; ++i) c += keys[i] == T ? 1u : 0u;
-    part[t] = c;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-        const uint32_t v = t >= off ? part[t - off] : 0u;
-        __syncthreads();
-        part[t] += v;
+    if (PASS < 2) {
+        for (int b = threadIdx.x; b < kSelWide; b += 1024) lh[b] = 0;
         __syncthreads();
     }
-    int64_t rank = int64_t(part[t] - c);
-    for (int64_t i = beg; i < end; ++i) {
-        const uint64_t key = keys[i];
-        uint8_t v = 0;
-        if (key > T) {
-            v = 1;
-        } else if (key == T) {
-            v = rank < r ? 1 : 0;
-            ++rank;
+    for (int64_t i = int64_t(blockIdx.x) * 1024 + threadIdx.x; i < n; i += int64_t(gridDim.x) * 1024) {
+        const uint64_t k = keys[i];
+        if (PASS == 0) {
+            atomicAdd(&lh[k >> 52], 1u);
+        } else if (PASS == 1) {
+            if (k >> 52 == prefix) atomicAdd(&lh[(k >> 40) & 4095], 1u);
+        } else if (k >> 40 == prefix) {
+            const uint32_t at = atomicAdd(&s->count, 1u);
+            if (at < kSelList) s->key[at] = k, s->index[at] = uint32_t(i);
         }
-        out[i] = v;
+    }
+    if (PASS < 2) {
+        __syncthreads();
+        for (int b = threadIdx.x; b < kSelWide; b += 1024)
+            if (lh[b]) atomicAdd(&s->hist[PASS][b], lh[b]);
+    }
+}
+
+__global__ __launch_bounds__(1024) void k_selw_cut(const uint64_t* __restrict__ keys, int64_t n, int64_t keep,
+                                                   SelWide* __restrict__ s) {
+    __shared__ SelShared sh;
+    int64_t r = keep;
+    uint64_t prefix = 0;
+    for (int p = 0; p < 2; ++p) {
+        sel_bin(s->hist[p], kSelWide, r, sh);
+        r -= sh.above;
+        prefix = prefix << 12 | uint64_t(sh.digit);
+        __syncthreads();
+    }
+    const uint64_t mask = ~((uint64_t(1) << 40) - 1);
+    const int64_t count = s->count;
+    const SelCut c =
+        count <= kSelList
+            ? sel_narrow([&](int64_t i) { return s->key[i]; }, [&](int64_t i) { return int64_t(s->index[i]); }, false,
+                         count, r, prefix << 40, mask, sh)
+            : sel_narrow([&](int64_t i) { return keys[i]; }, [](int64_t i) { return i; }, true, n, r, prefix << 40,
+                         mask, sh);
+    if (threadIdx.x == 0) s->cut = c;
+}
+
+__global__ __launch_bounds__(256) void k_selw_mark(const uint64_t* __restrict__ keys, int64_t n,
+                                                   const SelWide* __restrict__ s, uint8_t* __restrict__ out) {
+    const SelCut c = s->cut;
+    for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < n; i += int64_t(gridDim.x) * 256) {
+        const uint64_t k = keys[i];
+        out[i] = k > c.T || (k == c.T && i <= c.cut);
     }
 }
 
@@ -409,49 +598,66 @@ __global__ __launch_bounds__(256) void k_pack_seg(const int32_t* __restrict__ cn
 // Scatter of one reordered filter per wave: a kernel's slot is the start of
 // its pattern's segment + kept kernels of that pattern at lower ci.
 template <typename B>
-__global__ __launch_bounds__(64) void k_pack_scatter(const B* __restrict__ w,
-                                                     const uint8_t* __restrict__ pat,
-                                                     const uint8_t* __restrict__ keep, int cin,
-                                                     int64_t n_keep, PatTable tab, const int32_t* __restrict__ perm,
-                                                     const int32_t* __restrict__ seg,
-                                                     int32_t* __restrict__ cin_idx,
-                                                     uint8_t* __restrict__ pat_id,
-                                                     B* __restrict__ values) {
-    __shared__ int32_t cur[kMaxPatterns];
+__global__ __launch_bounds__(256) void k_pack_scatter(const B* __restrict__ w,
+                                                      const uint8_t* __restrict__ pat,
+                                                      const uint8_t* __restrict__ keep, int cin,
+                                                      int64_t n_keep, PatTable tab, const int32_t* __restrict__ perm,
+                                                      const int32_t* __restrict__ seg,
+                                                      int32_t* __restrict__ cin_idx,
+                                                      uint8_t* __restrict__ pat_id,
+                                                      B* __restrict__ values) {
+    // wave w takes the w-th quarter of the channels; cur[w][p]: the position
+    // of its next kernel of pattern p
+    __shared__ int32_t cur[4][kMaxPatterns];
     __shared__ uint16_t msk[kMaxPatterns];
-    const int i = blockIdx.x, lane = threadIdx.x, m = tab.m;
+    const int i = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m = tab.m;
     const int f = perm[i];
-    for (int p = lane; p < m; p += 64) {
-        cur[p] = seg[int64_t(i) * (m + 1) + p];
-        msk[p] = tab.mask[p];
+    for (int p = threadIdx.x; p < m; p += 256) msk[p] = tab.mask[p];
+    for (int p = lane; p < m; p += 64) cur[wave][p] = 0;
+    __syncthreads();
+    const int per = (cin + 255) / 256 * 64, lo = min(cin, wave * per), hi = min(cin, lo + per);
+    for (int ci = lo + lane; ci < hi; ci += 64) {
+        const int64_t k = int64_t(f) * cin + ci;
+        const int pp = pat[k];
+        if (keep[k] && pp < m) atomicAdd(&cur[wave][pp], 1);
     }
     __syncthreads();
-    for (int c0 = 0; c0 < cin; c0 += 64) {
-        const int ci = c0 + lane;
-        bool kept = false;
-        int pp = 0;
-        const int64_t k = int64_t(f) * cin + ci;
-        if (ci < cin) {
-            kept = keep[k] != 0;
-            pp = pat[k];
+    for (int p = threadIdx.x; p < m; p += 256) {
+        int32_t at = seg[int64_t(i) * (m + 1) + p];
+        for (int v = 0; v < 4; ++v) {
+            const int32_t c = cur[v][p];
+            cur[v][p] = at;
+            at += c;
         }
+    }
+    __syncthreads();
+    for (int c0 = lo; c0 < hi; c0 += 64) {
+        const int ci = c0 + lane;
+        const int64_t k = int64_t(f) * cin + ci;
+        const int pp = ci < hi ? pat[k] : kMaxPatterns;
+        const bool kept = ci < hi && keep[k] && pp < m;
+        // the lanes of one pattern at a time: their first lane's cursor, in
+        // lane order (a wave's LDS accesses are served in order)
+        uint64_t todo = __ballot(kept);
         int pos = -1;
-        for (int p = 0; p < m; ++p) {
-            const bool mine = kept && pp == p;
-            const uint64_t b = __ballot(mine);
-            if (b == 0) continue;
-            if (mine) pos = cur[p] + __popcll(b & ((uint64_t(1) << lane) - 1));
-            __syncthreads();
-            if (lane == 0) cur[p] += __popcll(b);
-            __syncthreads();
+        while (todo) {
+            const int p = __shfl(pp, __builtin_ctzll(todo));
+            const uint64_t b = __ballot(kept && pp == p);
+            if (kept && pp == p) pos = cur[wave][p] + __popcll(b & ((uint64_t(1) << lane) - 1));
+            if (lane == __builtin_ctzll(b)) cur[wave][p] += __popcll(b);
+            todo &= ~b;
         }
         if (kept && pos >= 0 && pos < n_keep) {   // a keep mask with too many ones writes nothing past the arrays
             cin_idx[pos] = ci;
             pat_id[pos] = uint8_t(pp);
-            const unsigned mk = msk[pp];
-            int j = 0;
-            for (int q = 0; q < 9; ++q)
-                if ((mk >> q) & 1u) values[int64_t(pos) * 4 + j++] = w[k * 9 + q];
+            unsigned mk = msk[pp];
+            B v[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                v[j] = w[k * 9 + __builtin_ctz(mk | 0x200u)];
+                mk &= mk - 1;
+            }
+            __builtin_memcpy(values + int64_t(pos) * 4, v, sizeof v);
         }
     }
 }
@@ -506,7 +712,8 @@ hipError_t launch_project(const PatTable& tab, int dtype, const void* w, int64_t
 
 size_t select_workspace_bytes(int64_t n_kernels) {
     const int64_t nblk = (n_kernels + kSelChunk - 1) / kSelChunk;
-    const size_t b = kSelCountOff + size_t(nblk) * 4;
+    const bool wide = n_kernels > kSelOneBlockMax && n_kernels <= kSelFastMax;
+    const size_t b = wide ? sizeof(SelWide) : kSelCountOff + size_t(nblk) * 4;
     return (b + 255) / 256 * 256;
 }
 
@@ -519,8 +726,23 @@ hipError_t launch_select(int64_t n, int64_t keep, const double* energy, uint8_t*
         return hipGetLastError();
     }
     if (n <= kSelOneBlockMax) {
-        hipLaunchKernelGGL(k_sel_one, dim3(1), dim3(1024), 0, stream, reinterpret_cast<const uint64_t*>(energy), n,
-                           keep, keep_out);
+        const uint64_t* const k = reinterpret_cast<const uint64_t*>(energy);
+        if (n <= 4096)
+            hipLaunchKernelGGL(k_sel_one<4>, dim3(1), dim3(1024), 0, stream, k, n, keep, keep_out);
+        else
+            hipLaunchKernelGGL(k_sel_one<16>, dim3(1), dim3(1024), 0, stream, k, n, keep, keep_out);
+        return hipGetLastError();
+    }
+    if (n <= kSelFastMax) {
+        const uint64_t* const k = reinterpret_cast<const uint64_t*>(energy);
+        SelWide* const s = static_cast<SelWide*>(ws);
+        const dim3 g(unsigned(grid_for(n, 4096, 256)));
+        hipLaunchKernelGGL(k_selw_clear, dim3(1), dim3(1024), 0, stream, s);
+        hipLaunchKernelGGL(k_selw_pass<0>, g, dim3(1024), 0, stream, k, n, keep, s);
+        hipLaunchKernelGGL(k_selw_pass<1>, g, dim3(1024), 0, stream, k, n, keep, s);
+        hipLaunchKernelGGL(k_selw_pass<2>, g, dim3(1024), 0, stream, k, n, keep, s);
+        hipLaunchKernelGGL(k_selw_cut, dim3(1), dim3(1024), 0, stream, k, n, keep, s);
+        hipLaunchKernelGGL(k_selw_mark, dim3(unsigned(grid_for(n, 256, 2048))), dim3(256), 0, stream, k, n, s, keep_out);
         return hipGetLastError();
     }
     char* base = static_cast<char*>(ws);
@@ -593,11 +815,11 @@ hipError_t launch_pack(const PatTable& tab, int dtype, int cout, int cin, int64_
     hipLaunchKernelGGL(k_pack_seg, dim3(g256), dim3(256), 0, stream, cnt, out.filter_perm,
                        out.filter_ptr, cout, m, out.seg_ptr);
     if (dtype == DT_F16)
-        hipLaunchKernelGGL(k_pack_scatter<uint16_t>, dim3(cout), dim3(64), 0, stream,
+        hipLaunchKernelGGL(k_pack_scatter<uint16_t>, dim3(cout), dim3(256), 0, stream,
                            static_cast<const uint16_t*>(w), pat, keep, cin, n_keep, tab, out.filter_perm,
                            out.seg_ptr, out.cin_idx, out.pat_id, static_cast<uint16_t*>(out.values));
     else
-        hipLaunchKernelGGL(k_pack_scatter<uint32_t>, dim3(cout), dim3(64), 0, stream,
+        hipLaunchKernelGGL(k_pack_scatter<uint32_t>, dim3(cout), dim3(256), 0, stream,
                            static_cast<const uint32_t*>(w), pat, keep, cin, n_keep, tab, out.filter_perm,
                            out.seg_ptr, out.cin_idx, out.pat_id, static_cast<uint32_t*>(out.values));
     return hipGetLastError();
