@@ -123,7 +123,9 @@ class Net:
             if lay.pool_after:
                 pooled = torch.empty((n, lay.cout, lay.h // 2, lay.w // 2), dtype=tdt, device="cuda")
             cfg = B.conv3x3_config(prep.layer, prep.layer.dtype, n, lay.h, lay.w, False, lay.stride, algo)
-            self.layers.append(dict(lay=lay, w=w, prep=prep, x=x, y=y, pooled=pooled, fused=False, cfg=cfg))
+            mfma = algo == 0 and B.conv3x3_on_matrix_cores(prep.layer, prep.layer.dtype, n, lay.h, lay.w, False,
+                                                           lay.stride)
+            self.layers.append(dict(lay=lay, w=w, prep=prep, x=x, y=y, pooled=pooled, fused=False, cfg=cfg, mfma=mfma))
             if wl.chained:
                 x = pooled if pooled is not None else y
         torch.cuda.synchronize()
@@ -257,7 +259,8 @@ def layer_table(net, miopen):
         row = dict(layer=lay.name, cin=lay.cin, cout=lay.cout, h=lay.h, w=lay.w, stride=lay.stride, keep=lay.keep,
                    fused_pool=bool(L["fused"]), ms=round(med, 5), p10=round(p10, 5), p90=round(p90, 5),
                    mean_ms=round(mean, 5), nz_gflops=round(nz / (med * 1e-3) / 1e9, 1),
-                   kernel=["stream", "wide", "simple", "stride2", "rows"][L["cfg"]["kernel"]] + ("-staged" if L["cfg"]["staged"] else ""),
+                   kernel="mfma" if L["mfma"] and not L["fused"] else
+                   ["stream", "wide", "simple", "stride2", "rows"][L["cfg"]["kernel"]] + ("-staged" if L["cfg"]["staged"] else ""),
                    R=L["cfg"]["rows_per_lane"], KS=L["cfg"]["shares"])
         if "fusion_us" in L:
             row["pool_separate_fused_us"] = L["fusion_us"]

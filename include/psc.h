@@ -211,12 +211,13 @@ psc_status psc_conv3x3_fwd_strided(const psc_layer *layer, const psc_packed *pac
 
 /* psc_conv3x3_fwd (pool 0, stride 1), _pool2 (pool != 0) or _strided with a
  * scratch buffer of the caller's, at least psc_conv3x3_workspace bytes and
- * 256-byte aligned (NULL: exactly those calls).  With it algo 0 may run fp16
+ * 256-byte aligned (NULL: exactly those calls).  With it algo 0 may run
  * layers on the matrix cores: each call then decodes the packed weights into
- * the buffer and multiplies the dense tiles, with the same products and fp32
- * sums.  The buffer holds nothing from one call to the next.  Calls on the
- * same *packed may share one buffer, also on several streams (each writes the
- * same bytes); calls on different ones that may overlap need one each. */
+ * the buffer and multiplies the dense tiles, fp16 values as they are and fp32
+ * values in three bf16 parts whose sum is exact, with fp32 sums.  The buffer
+ * holds nothing from one call to the next.  Calls on the same *packed may
+ * share one buffer, also on several streams (each writes the same bytes);
+ * calls on different ones that may overlap need one each. */
 psc_status psc_conv3x3_workspace(const psc_layer *layer, size_t *bytes);
 /* *out = 1 where psc_conv3x3_fwd_ws with algo 0 runs the matrix-core kernel
  * (host only, arguments validated as by psc_conv3x3_config). */
@@ -301,9 +302,9 @@ psc_status psc_admm_residual(const float *d_z, const float *d_target, int64_t nu
  *   d_dw[o][i][r][s] = sum over images and pixels of
  *                      g[n, o, h, w] * x[n, i, h + r - 1, w + s - 1]
  * and, if d_db is non-NULL, d_db[o] = sum of g[n, o, :, :]; fp32.  Layers of
- * at least 16 input channels run on the matrix cores (fp32 MFMA), the others
- * on the vector ALUs; partial sums are added in a fixed order, so results
- * are deterministic.  Workspace as for psc_conv3x3_bwd_weight
+ * at least 16 input channels run on the matrix cores (each value in three bf16
+ * parts whose sum is exact), the others on the vector ALUs; partial sums are
+ * added in a fixed order, so results are deterministic.  Workspace as for psc_conv3x3_bwd_weight
  * (psc_dense3x3_bwd_weight_workspace bytes); x and g of more than 2 GiB
  * each return PSC_ERR_UNSUPPORTED. */
 psc_status psc_dense3x3_bwd_weight_workspace(int32_t n, int32_t cin, int32_t h, int32_t w,
@@ -360,10 +361,21 @@ psc_status psc_conv3x3_config(const psc_layer *layer, int32_t act_dtype, int32_t
  * convolution (stride 1, pad 1) of dense OIHW weights d_w [cout][cin][3][3],
  * same conventions as psc_conv3x3_fwd, fp32 accumulation (fp16 inputs
  * widened exactly).  Layers of more than 8 input channels run on the matrix
- * cores (fp32 MFMA), the others on the vector ALUs. */
+ * cores (fp32 MFMA; with scratch see psc_dense3x3_fwd_ws), the others on the
+ * vector ALUs. */
 psc_status psc_dense3x3_fwd(int32_t dtype, const void *d_x, int32_t n, int32_t cin,
                             int32_t h, int32_t w, const void *d_w, int32_t cout,
                             const void *d_bias, int32_t relu, void *d_y, void *stream);
+
+/* The same with a scratch buffer of the caller's, at least
+ * psc_dense3x3_fwd_workspace bytes and 256-byte aligned (NULL: exactly that
+ * call).  With it fp32 layers of at least 16 input channels and 32 filters run
+ * on the 16-bit matrix cores, each value in three bf16 parts whose sum is exact. */
+psc_status psc_dense3x3_fwd_workspace(int32_t dtype, int32_t cin, int32_t cout, size_t *bytes);
+psc_status psc_dense3x3_fwd_ws(int32_t dtype, const void *d_x, int32_t n, int32_t cin,
+                               int32_t h, int32_t w, const void *d_w, int32_t cout,
+                               const void *d_bias, int32_t relu, void *d_y, void *d_ws,
+                               size_t ws_bytes, void *stream);
 
 /* 2x2 max-pool, stride 2 (the pooling of the VGG-16 stack): d_x
  * [n][c][h][w] -> d_y [n][c][h/2][w/2]; h and w must be even. */

@@ -113,6 +113,8 @@ def lib() -> ctypes.CDLL:
         "psc_admm_primal": ([i64, P, P, P, P, i32, P, P, ctypes.c_float, ctypes.c_float, P, P], ctypes.c_int),
         "psc_admm_dual": ([LP, P, P, P, P, P, P], ctypes.c_int),
         "psc_dense3x3_fwd": ([i32, P, i32, i32, i32, i32, P, i32, P, i32, P, P], ctypes.c_int),
+        "psc_dense3x3_fwd_workspace": ([i32, i32, i32, ctypes.POINTER(sz)], ctypes.c_int),
+        "psc_dense3x3_fwd_ws": ([i32, P, i32, i32, i32, i32, P, i32, P, i32, P, P, sz, P], ctypes.c_int),
         "psc_maxpool2x2": ([i32, P, i32, i32, i32, i32, P, P], ctypes.c_int),
     }
     for name, (args, res) in sig.items():
@@ -330,14 +332,24 @@ def conv3x3_on_matrix_cores(layer: Layer, dtype: int, n: int, h: int, w: int, po
     return bool(out.value)
 
 
-def dense3x3_fwd(x, wd, y, bias=None, relu: bool = False, stream=None):
+def dense3x3_fwd(x, wd, y, bias=None, relu: bool = False, stream=None, ws=None):
+    """psc_dense3x3_fwd, or psc_dense3x3_fwd_ws with the scratch tensor ``ws``
+    (dense3x3_fwd_workspace)."""
     n, cin, h, w = (int(d) for d in x.shape)
     cout = int(wd.shape[0])
     if tuple(wd.shape) != (cout, cin, 3, 3) or tuple(y.shape) != (n, cout, h, w):
         raise ValueError("shape mismatch")
-    _check(lib().psc_dense3x3_fwd(dtype_code(x), _dev(x, "x"), n, cin, h, w, _dev(wd, "w"), cout,
-                                  _dev(bias, "bias"), int(bool(relu)), _dev(y, "y"), _stream(stream)),
-           "psc_dense3x3_fwd")
+    _check(lib().psc_dense3x3_fwd_ws(dtype_code(x), _dev(x, "x"), n, cin, h, w, _dev(wd, "w"), cout,
+                                     _dev(bias, "bias"), int(bool(relu)), _dev(y, "y"), _dev(ws, "ws"),
+                                     _ws_bytes(ws), _stream(stream)), "psc_dense3x3_fwd")
+
+
+def dense3x3_fwd_workspace(dtype: int, cin: int, cout: int, device="cuda"):
+    """A scratch tensor for dense3x3_fwd (None if it has no use for one)."""
+    b = ctypes.c_size_t(0)
+    _check(lib().psc_dense3x3_fwd_workspace(int(dtype), int(cin), int(cout), ctypes.byref(b)),
+           "psc_dense3x3_fwd_workspace")
+    return None if b.value == 0 else _torch().empty(int(b.value), dtype=_torch().uint8, device=device)
 
 
 def probe_fma(blocks: int, iters: int, out, stream=None):
@@ -476,6 +488,7 @@ class AdmmLayer:
         self.energy = torch.empty(K, dtype=torch.float64, device=w0.device)
         self.keep_mask = torch.empty(K, dtype=torch.uint8, device=w0.device)
         self.ws_sel = None if noalloc else workspace(self.layer, PSC_OP_SELECT, w0.device)
+        self.ws_dense = dense3x3_fwd_workspace(PSC_F32, cin, cout, w0.device)
         self.ws_res = torch.empty(ADMM_RESIDUAL_WS_BYTES, dtype=torch.uint8, device=w0.device)
         self.loss = torch.zeros(1, dtype=torch.float64, device=w0.device)
         self.lr, self.k = float(lr), 0
@@ -492,7 +505,7 @@ class AdmmLayer:
         """X' = relu(W0 X + b0): the pre-trained layer's output."""
         n, _, h, w = x.shape
         out = out if out is not None else self._buf("target", (n, self.layer.cout, h, w))
-        dense3x3_fwd(x, self.w0, out, bias=self.b0, relu=True, stream=stream)
+        dense3x3_fwd(x, self.w0, out, bias=self.b0, relu=True, stream=stream, ws=self.ws_dense)
         return out
 
     def iteration(self, x, target, rho: float, scale: float, stream=None):
@@ -500,7 +513,7 @@ class AdmmLayer:
         n, _, h, w = x.shape
         z = self._buf("z", (n, self.layer.cout, h, w))
         g = self._buf("g", (n, self.layer.cout, h, w))
-        dense3x3_fwd(x, self.w, z, bias=self.b, relu=False, stream=stream)
+        dense3x3_fwd(x, self.w, z, bias=self.b, relu=False, stream=stream, ws=self.ws_dense)
         admm_residual(z, target, scale, g, self.loss, self.ws_res, stream)
         ws = self._bufs.get("wgrad_ws")
         need = dense3x3_bwd_weight_workspace(n, self.layer.cin, h, w, self.layer.cout, x.device) \

@@ -37,37 +37,18 @@
 // Layout of v_mfma_f32_32x32x16_f16: lane l supplies A[l % 32][8 (l / 32) + j]
 // and B[8 (l / 32) + j][l % 32], j = 0..7; register r of the result holds
 // D[8 (r / 4) + 4 (l / 32) + r % 4][l % 32].
-#include <cstring>
-
-#include "common.h"
-#include "launch.h"
+#include "conv_mfma.h"
 
 namespace psc {
 namespace {
+using namespace cm;
 
-constexpr int kF = 64;         // filters per block
 constexpr int kKC = 32, kQ = kKC / 8;   // channels of a weight chunk and per four waves and stage
 
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 typedef float f16v __attribute__((ext_vector_type(16)));
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u2 __attribute__((ext_vector_type(2)));
-
-struct MGeo {
-    int n, cin, H, W, cout, m, relu, keep;
-    int S;              // stride
-    int OH, OW;
-    int CT, TW;         // column strips and output columns of one
-    int P;              // positions of a tile row: S * TW + 2
-    int Lst;            // positions of the X tile (its stride between channel groups)
-    int slots;          // output slots of a strip: n * OH * TW
-    int ptiles;         // pixel tiles of a strip
-    int ftiles;
-    int nblocks;
-    int chunks;         // 32-channel chunks of the weight tiles: an even number
-    int x_bytes;
-    uint16_t taps[kMaxPatterns];   // a pattern's 4 taps, 4 bits each, ascending
-};
 
 // The weight tiles of a call, decoded from the compressed storage:
 //   wt[f / 64][c / 32][tap][(c / 8) % 4][f % 64][c % 8],
@@ -408,60 +389,17 @@ __global__ __launch_bounds__(256 * G, 2) void k_conv_mfma(
         }
 }
 
-// The pixel tile and geometry of a call; false when the kernel does not take
-// it.  Host only.
-struct MPlan {
-    MGeo g;
-    int NT, G, MI;
-    bool aligned;
-    size_t lds;
-};
-
+// A tile of NT pixels and G groups of waves; false when the kernel does not
+// take it.  Host only.
 bool tile_plan(const ConvArgs& a, int m, int NT, int G, MPlan& p) {
     const int kThreads = 256 * G, KC = kKC * G;
+    int64_t rows;
+    if (!geometry(a, m, NT, p, rows)) return false;
     MGeo& g = p.g;
-    g.n = a.n;
-    g.cin = a.cin;
-    g.H = a.h;
-    g.W = a.w;
-    g.cout = a.cout;
-    g.m = m;
-    g.relu = a.relu;
-    g.keep = int(a.keep);
-    g.chunks = (a.cin + 63) / 64 * 2;
-    g.S = a.stride;
-    g.OH = (a.h - 1) / a.stride + 1;
-    g.OW = (a.w - 1) / a.stride + 1;
-    g.x_bytes = int(int64_t(a.n) * a.cin * a.h * a.w * 2);
-    // strips of at most 32 output columns; 4-column loads are aligned where
-    // rows and strips are multiples of 4 columns
-    g.CT = (g.OW + 31) / 32;
-    g.TW = (g.OW + g.CT - 1) / g.CT;
-    p.aligned = a.w % 4 == 0 && reinterpret_cast<uintptr_t>(a.x) % 8 == 0;
-    if (p.aligned && g.CT > 1) g.TW = (g.TW + 3) / 4 * 4;
-    g.CT = (g.OW + g.TW - 1) / g.TW;
-    if (a.w - g.S * (g.CT - 1) * g.TW < 4) return false;     // a strip narrower than one vector
-    g.P = g.S * g.TW + 2;
-    const int64_t slots = int64_t(a.n) * g.OH * g.TW;
-    if (slots * g.CT > 0x3fffffff) return false;
-    g.slots = int(slots);
-    g.ptiles = int((slots + NT - 1) / NT);
-    g.ftiles = (a.cout + kF - 1) / kF;
-    const int64_t blocks = int64_t(g.ptiles) * g.CT * g.ftiles;
-    if (blocks > 0x3fffffff) return false;
-    g.nblocks = int(blocks);
-    // padded rows of the largest tile: NT slots touch at most orows output
-    // rows and cross at most `cross` image boundaries
-    int64_t orows = (NT - 2) / g.TW + 2;
-    if (orows > int64_t(a.n) * g.OH) orows = int64_t(a.n) * g.OH;
-    const int64_t cross = (orows + g.OH - 2) / g.OH;
-    const int64_t rows = g.S * (orows - 1) + 3 + cross * (a.h + 1 - g.S * g.OH);
-    g.Lst = int(rows * g.P);
     const int64_t items = (KC / 8) * rows * ((g.S * g.TW + 3) / 4);
     const int64_t per = (items + kThreads - 1) / kThreads;
     p.MI = per <= 2 ? 2 : 4;
     if (per > p.MI || (g.CT > 1 && (KC / 8) * rows * 2 > kThreads)) return false;
-    p.NT = NT;
     p.G = G;
     p.lds = size_t(9 * (KC / 8) * kF * 16) + size_t(KC / 8) * g.Lst * 16;
     return p.lds <= 136 * 1024;
@@ -478,15 +416,11 @@ bool plan_conv_mfma(const PatTable& tab, const ConvArgs& a, MPlan& p) {
     // dense work.  Measured both ways on 30 layers; those within 15 % stay.
     const double outs = double(a.n) * ((a.h - 1) / a.stride + 1) * ((a.w - 1) / a.stride + 1);
     const double valu_us = 7.0 + 8.0 * outs * double(a.keep) / 30e6;
-    const double dense_us = 18.0 * outs * a.cin * a.cout / 700e6, chain_us = 3.0 * ((a.cin + 63) / 64);
+    const double padded = double((a.cin + 31) / 32 * 32) * ((a.cout + 63) / 64 * 64);
+    const double dense_us = 18.0 * outs * padded / 700e6, chain_us = 3.0 * ((a.cin + 63) / 64);
     if (1.15 * (6.0 + (dense_us > chain_us ? dense_us : chain_us)) > valu_us) return false;
     std::memset(&p, 0, sizeof p);
-    for (int i = 0; i < tab.m; ++i) {
-        uint32_t t = 0, k = 0;
-        for (uint32_t q = 0; q < 9; ++q)
-            if ((tab.mask[i] >> q) & 1) t |= q << (4 * k++);
-        p.g.taps[i] = uint16_t(t);
-    }
+    pack_taps(tab, p.g);
     // The largest tile that still gives each CU about 1.5 blocks (2 fit);
     // else about one block per CU, of 8 waves that take 64 channels a stage
     // (256 @ 14x14 at batch 32: 22.7 us, against 24.5 in 4-wave blocks of half
@@ -517,11 +451,13 @@ hipError_t launch_nt(const MPlan& p, const PackedView& pk, const ConvArgs& a, hi
 }  // namespace
 
 size_t conv_workspace_bytes(int dtype, int cout, int cin) {
-    if (dtype != DT_F16 || cin < 16 || cout < 32) return 0;
+    if (cin < 16 || cout < 32) return 0;
+    if (dtype == DT_F32) return split_tiles_bytes(cout, cin);
     return size_t((cout + kF - 1) / kF) * size_t((cin + 63) / 64 * 2) * (9 * kKC * kF * 2);
 }
 
 bool conv_mfma_takes(const PatTable& tab, const ConvArgs& a) {
+    if (a.dtype == DT_F32) return conv_split_takes(tab, a);
     MPlan p;
     return plan_conv_mfma(tab, a, p);
 }

@@ -14,6 +14,8 @@ bool describe_conv_stride2(const PatTable& tab, const ConvArgs& a, ConvForm& out
 hipError_t launch_conv_rows(const PatTable& tab, const PackedView& pk, const ConvArgs& a, hipStream_t stream);
 bool describe_conv_rows(const PatTable& tab, const ConvArgs& a, ConvForm& out);
 bool prefer_conv_rows(const PatTable& tab, const ConvArgs& a);
+hipError_t launch_conv_split(const PatTable& tab, const PackedView& pk, const ConvArgs& a, hipStream_t stream);
+hipError_t launch_dense_split(const ConvArgs& a, const void* w, hipStream_t stream);
 hipError_t launch_conv_mfma(const PatTable& tab, const PackedView& pk, const ConvArgs& a, hipStream_t stream);
 
 namespace {
@@ -360,7 +362,8 @@ hipError_t conv_simple(const PatTable& tab, const PackedView& pk, const ConvArgs
 hipError_t launch_conv(const PatTable& tab, const PackedView& pk, const ConvArgs& a, int algo,
                        hipStream_t stream) {
     if (algo == 0) {
-        const hipError_t e = launch_conv_mfma(tab, pk, a, stream);
+        const hipError_t e = a.dtype == DT_F16 ? launch_conv_mfma(tab, pk, a, stream)
+                                               : launch_conv_split(tab, pk, a, stream);
         if (e != hipErrorNotSupported) return e;
     }
     // algo 2: the one-row-per-lane kernel (the caller has checked that it
@@ -400,7 +403,12 @@ void describe_conv(const PatTable& tab, const ConvArgs& a, int algo, ConvForm& o
 }
 
 hipError_t launch_dense(int dtype, const void* x, int n, int cin, int h, int w, const void* wd, int cout,
-                        const void* bias, int relu, void* y, hipStream_t stream) {
+                        const void* bias, int relu, void* y, void* ws, size_t ws_bytes, hipStream_t stream) {
+    if (ws) {
+        const ConvArgs a{dtype, n, cin, h, w, cout, 0, x, bias, relu, y, 0, 1, ws, ws_bytes};
+        const hipError_t e = launch_dense_split(a, wd, stream);
+        if (e != hipErrorNotSupported) return e;
+    }
     // the matrix-core kernel addresses x and the weights through 32-bit
     // buffer offsets
     const int esz = dtype == DT_F16 ? 2 : 4;

@@ -136,7 +136,11 @@ hipError_t launch_admm_dual(const PatTable& tab, const float* v, const uint8_t* 
                             float* a, float* d, hipStream_t stream);
 
 hipError_t launch_dense(int dtype, const void* x, int n, int cin, int h, int w, const void* wd,
-                        int cout, const void* bias, int relu, void* y, hipStream_t stream);
+                        int cout, const void* bias, int relu, void* y, void* ws, size_t ws_bytes,
+                        hipStream_t stream);
+// Scratch bytes of the weight tiles of an fp32 layer on the 16-bit matrix cores.
+size_t split_tiles_bytes(int cout, int cin);
+bool conv_split_takes(const PatTable& tab, const ConvArgs& a);
 hipError_t launch_maxpool(int dtype, const void* x, int n, int c, int h, int w, void* y,
                           hipStream_t stream);
 

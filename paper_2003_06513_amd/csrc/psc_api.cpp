@@ -548,9 +548,9 @@ psc_status psc_admm_dual(const psc_layer* L, const float* d_v, const uint8_t* d_
                          "psc_admm_dual launch");
 }
 
-psc_status psc_dense3x3_fwd(int32_t dtype, const void* d_x, int32_t n, int32_t cin, int32_t h,
-                            int32_t w, const void* d_w, int32_t cout, const void* d_bias,
-                            int32_t relu, void* d_y, void* stream) {
+psc_status psc_dense3x3_fwd_ws(int32_t dtype, const void* d_x, int32_t n, int32_t cin, int32_t h,
+                               int32_t w, const void* d_w, int32_t cout, const void* d_bias,
+                               int32_t relu, void* d_y, void* d_ws, size_t ws_bytes, void* stream) {
     if (!dtype_ok(dtype)) return fail(PSC_ERR_ARG, "dtype=%d is not a psc_dtype", dtype);
     if (n < 0 || n > 65535 || cin < 1 || cout < 1 || cout > 65535 || h < 1 || w < 1 ||
         h > 32768 || w > 32768)
@@ -564,9 +564,26 @@ psc_status psc_dense3x3_fwd(int32_t dtype, const void* d_x, int32_t n, int32_t c
     const size_t es = elt_size(dtype);
     if (overlaps(d_x, size_t(int64_t(n) * cin * plane) * es, d_y, size_t(int64_t(n) * cout * plane) * es))
         return fail(PSC_ERR_ARG, "d_y overlaps d_x");
+    if (reinterpret_cast<uintptr_t>(d_ws) & 255u)
+        return fail(PSC_ERR_WORKSPACE, "workspace must be 256-byte aligned");
     return device_status(psc::launch_dense(dtype, d_x, n, cin, h, w, d_w, cout, d_bias, relu != 0,
-                                           d_y, as_stream(stream)),
+                                           d_y, d_ws, ws_bytes, as_stream(stream)),
                          "psc_dense3x3_fwd launch");
+}
+
+psc_status psc_dense3x3_fwd(int32_t dtype, const void* d_x, int32_t n, int32_t cin, int32_t h,
+                            int32_t w, const void* d_w, int32_t cout, const void* d_bias,
+                            int32_t relu, void* d_y, void* stream) {
+    return psc_dense3x3_fwd_ws(dtype, d_x, n, cin, h, w, d_w, cout, d_bias, relu, d_y, nullptr, 0, stream);
+}
+
+psc_status psc_dense3x3_fwd_workspace(int32_t dtype, int32_t cin, int32_t cout, size_t* bytes) {
+    if (!dtype_ok(dtype)) return fail(PSC_ERR_ARG, "dtype=%d is not a psc_dtype", dtype);
+    if (cin < 1 || cout < 1 || cout > 65535 || int64_t(cout) * cin * 9 > kMaxElems)
+        return fail(PSC_ERR_ARG, "bad shape cin=%d cout=%d", cin, cout);
+    if (!bytes) return fail(PSC_ERR_ARG, "bytes is NULL");
+    *bytes = dtype == PSC_F32 && cin >= 16 && cout >= 32 ? psc::split_tiles_bytes(cout, cin) : 0;
+    return ok();
 }
 
 psc_status psc_maxpool2x2(int32_t dtype, const void* d_x, int32_t n, int32_t c, int32_t h, int32_t w,

@@ -297,8 +297,10 @@ static size_t wgrad_part_bytes(const WGeo& g, int64_t nk, bool dense) {
 // 254 -> 157), which puts the lines at 18 and 25 % of the kernels.
 static bool masked_via_dense(int n, int cin, int cout, int h, int w, int64_t keep, int dtype, DenseWPlan* dp) {
     if (!dense_wgrad_mfma_plan(n, cin, cout, h, w, dtype, dp)) return false;
+    // the padding of channels, filters and columns counts as dense work
     const int64_t cols = (w + 7) / 8 * 8, line = dtype == DT_F16 ? 18 : 25;
-    return n == 1 || 100 * keep * w >= line * cin * cout * cols;
+    const int64_t pairs = int64_t((cin + 31) / 32 * 32) * ((cout + 31) / 32 * 32);
+    return n == 1 || double(100 * keep) * w >= double(line * pairs) * cols;
 }
 
 size_t wgrad_workspace_bytes(int n, int cin, int cout, int h, int w, int64_t nk, bool dense, int dtype) {
