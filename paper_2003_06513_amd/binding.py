@@ -191,6 +191,8 @@ class Layer:
 class Packed:
     """Compressed weight storage held in device tensors (psc_packed)."""
 
+    work, work_bytes = None, 0      # also of an instance restored without them
+
     def __init__(self, layer: Layer, device="cuda"):
         torch = _torch()
         cout, m, keep = layer.cout, layer.m, layer.keep

@@ -53,41 +53,51 @@ typedef uint32_t u2 __attribute__((ext_vector_type(2)));
 // The weight tiles of a call, decoded from the compressed storage:
 //   wt[f / 64][c / 32][tap][(c / 8) % 4][f % 64][c % 8],
 // zero where pruned and past cin and cout; f counts reordered filters.  A
-// block owns 8 filters x 128 channels: its waves scan their 2 filters'
-// kernels, scatter the weights to LDS and write 16-byte units.
+// block owns 8 filters x 128 channels: each of its waves scans a filter's
+// kernels, scatters the weights to LDS, and all write 16-byte units.
 constexpr int kDF = 8, kDC = 128;
 
-__global__ __launch_bounds__(256) void k_weight_tiles(const int32_t* __restrict__ fptr,
+__global__ __launch_bounds__(512) void k_weight_tiles(const int32_t* __restrict__ fptr,
                                                       const int32_t* __restrict__ cin_idx,
                                                       const uint8_t* __restrict__ pat_id,
                                                       const uint16_t* __restrict__ values, MGeo g,
                                                       uint16_t* __restrict__ wt) {
     __shared__ __align__(16) uint16_t t[kDF][9 * kDC];
     const int f0 = blockIdx.x * kDF, c0 = blockIdx.y * kDC;
-    for (int e = threadIdx.x; e < kDF * 9 * kDC / 8; e += 256) reinterpret_cast<u4*>(t)[e] = u4{0, 0, 0, 0};
+    for (int e = threadIdx.x; e < kDF * 9 * kDC / 8; e += 512) reinterpret_cast<u4*>(t)[e] = u4{0, 0, 0, 0};
     __syncthreads();
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int i = 0; i < 2; ++i) {
-        const int fl = 2 * wave + i;
-        if (f0 + fl >= g.cout) continue;
+    const int lane = threadIdx.x & 63, fl = threadIdx.x >> 6;
+    if (f0 + fl < g.cout) {
         const int k0 = fptr[f0 + fl] > 0 ? fptr[f0 + fl] : 0;
         const int k1 = fptr[f0 + fl + 1] < g.keep ? fptr[f0 + fl + 1] : g.keep;
-        for (int k = k0 + lane; k < k1; k += 64) {
-            const int c = cin_idx[k] - c0, p = pat_id[k];
-            if (uint32_t(c) >= uint32_t(kDC) || c0 + c >= g.cin || p >= g.m) continue;
-            uint32_t v[2];
-            __builtin_memcpy(v, values + 4 * int64_t(k), 8);
-            const uint32_t tp = g.taps[p];
-            t[fl][(tp & 15) * kDC + c] = uint16_t(v[0]);
-            t[fl][((tp >> 4) & 15) * kDC + c] = uint16_t(v[0] >> 16);
-            t[fl][((tp >> 8) & 15) * kDC + c] = uint16_t(v[1]);
-            t[fl][(tp >> 12) * kDC + c] = uint16_t(v[1] >> 16);
+        // four kernels a lane in flight, weights with their indices: one
+        // memory latency where a filter keeps up to 256 kernels
+        for (int kb = k0; kb < k1; kb += 256) {
+            int c[4], p[4];
+            uint32_t v[4][2];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int k = kb + 64 * j + lane < k1 ? kb + 64 * j + lane : k0;
+                c[j] = cin_idx[k] - c0;
+                p[j] = pat_id[k];
+                __builtin_memcpy(v[j], values + 4 * int64_t(k), 8);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (kb + 64 * j + lane >= k1 || uint32_t(c[j]) >= uint32_t(kDC) || c0 + c[j] >= g.cin || p[j] >= g.m)
+                    continue;
+                const uint32_t tp = g.taps[p[j]];
+                t[fl][(tp & 15) * kDC + c[j]] = uint16_t(v[j][0]);
+                t[fl][((tp >> 4) & 15) * kDC + c[j]] = uint16_t(v[j][0] >> 16);
+                t[fl][((tp >> 8) & 15) * kDC + c[j]] = uint16_t(v[j][1]);
+                t[fl][(tp >> 12) * kDC + c[j]] = uint16_t(v[j][1] >> 16);
+            }
         }
     }
     __syncthreads();
     // unit (filter, tap, 8 channels): neighbouring lanes take the 8 filters
     const int nst = g.chunks;
-    for (int e = threadIdx.x; e < kDF * 9 * kDC / 8; e += 256) {
+    for (int e = threadIdx.x; e < kDF * 9 * kDC / 8; e += 512) {
         const int fl = e % kDF, u = e / kDF, cg = u % (kDC / 8), q = u / (kDC / 8);
         const int f = f0 + fl, st = c0 / kKC + cg / (kKC / 8);
         if (st >= nst) continue;
@@ -467,7 +477,7 @@ hipError_t launch_conv_mfma(const PatTable& tab, const PackedView& pk, const Con
     if (!a.ws || a.ws_bytes < conv_workspace_bytes(a.dtype, a.cout, a.cin) || !plan_conv_mfma(tab, a, p))
         return hipErrorNotSupported;
     const dim3 grid(unsigned((p.g.ftiles * kF) / kDF), unsigned((a.cin + kDC - 1) / kDC));
-    hipLaunchKernelGGL(k_weight_tiles, grid, dim3(256), 0, s, pk.filter_ptr, pk.cin_idx, pk.pat_id,
+    hipLaunchKernelGGL(k_weight_tiles, grid, dim3(512), 0, s, pk.filter_ptr, pk.cin_idx, pk.pat_id,
                        static_cast<const uint16_t*>(pk.values), p.g, static_cast<uint16_t*>(a.ws));
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -102,12 +102,25 @@ __global__ __launch_bounds__(256) void k_split_packed(const int32_t* __restrict_
     if (f0 + fl < g.cout) {
         const int k0 = fptr[f0 + fl] > 0 ? fptr[f0 + fl] : 0;
         const int k1 = fptr[f0 + fl + 1] < g.keep ? fptr[f0 + fl + 1] : g.keep;
-        for (int k = k0 + lane; k < k1; k += 64) {
-            const int c = cin_idx[k] - c0, p = pat_id[k];
-            if (uint32_t(c) >= uint32_t(kDC) || c0 + c >= g.cin || p >= g.m) continue;
-            const uint32_t tp = g.taps[p];
+        // four kernels a lane in flight, weights with their indices
+        for (int kb = k0; kb < k1; kb += 256) {
+            int c[4], p[4];
+            float v[4][4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) t[fl][((tp >> (4 * j)) & 15) * kDC + c] = values[4 * int64_t(k) + j];
+            for (int i = 0; i < 4; ++i) {
+                const int k = kb + 64 * i + lane < k1 ? kb + 64 * i + lane : k0;
+                c[i] = cin_idx[k] - c0;
+                p[i] = pat_id[k];
+                __builtin_memcpy(v[i], values + 4 * int64_t(k), 16);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (kb + 64 * i + lane >= k1 || uint32_t(c[i]) >= uint32_t(kDC) || c0 + c[i] >= g.cin || p[i] >= g.m)
+                    continue;
+                const uint32_t tp = g.taps[p[i]];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) t[fl][((tp >> (4 * j)) & 15) * kDC + c[i]] = v[i][j];
+            }
         }
     }
     __syncthreads();
