@@ -281,21 +281,21 @@ __device__ __forceinline__ void sel_bin(const uint32_t* hist, int bins, int64_t 
 }
 
 // T and cut of the r largest of n candidates (those that match the decided
-// bits `mask` of `prefix`; 1 <= r <= their number).  key(i) and index(i) name
-// the i-th key and its index; `ordered`: index(i) ascends with i.  All 1024
-// threads call it.
-template <typename Key, typename Index>
-__device__ SelCut sel_narrow(Key key, Index index, bool ordered, int64_t n, int64_t r, uint64_t prefix, uint64_t mask,
+// bits `mask` of `prefix`; 1 <= r <= their number).  each(f) calls f on the
+// thread's share of the keys; key(i) and index(i) name the i-th key and its
+// index, for ties; `ordered`: index(i) ascends with i.  All 1024 threads call
+// it.
+template <typename Each, typename Key, typename Index>
+__device__ SelCut sel_narrow(Each each, Key key, Index index, bool ordered, int64_t n, int64_t r, uint64_t prefix, uint64_t mask,
                              SelShared& sh) {
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     uint64_t T = 0;
     bool all = false;                                    // every candidate that is left is kept
     for (;;) {
         uint64_t va = ~uint64_t(0), vo = 0;
-        for (int64_t i = t; i < n; i += 1024) {
-            const uint64_t k = key(i);
+        each([&](uint64_t k) {
             if ((k & mask) == prefix) va &= k, vo |= k;
-        }
+        });
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) {
             va &= uint64_t(__shfl_xor((unsigned long long)va, off));
@@ -314,10 +314,9 @@ __device__ SelCut sel_narrow(Key key, Index index, bool ordered, int64_t n, int6
         const uint64_t low = (uint64_t(2) << hb) - 1;    // all ones for hb = 63
         mask = ~low;
         prefix = va & mask;
-        for (int64_t i = t; i < n; i += 1024) {
-            const uint64_t k = key(i);
+        each([&](uint64_t k) {
             if ((k & mask) == prefix) atomicAdd(&sh.hist[(k & low) >> shift], 1u);
-        }
+        });
         __syncthreads();
         sel_bin(sh.hist, kSelBins, r, sh);
         const int d = sh.digit;
@@ -364,8 +363,9 @@ __device__ SelCut sel_narrow(Key key, Index index, bool ordered, int64_t n, int6
     return SelCut{T, sh.cut};
 }
 
-// The whole selection in one workgroup (at most kSelOneBlockMax keys, up to
-// 16 of them in each thread's registers).
+// The whole selection in one workgroup, KPT keys in each thread's registers:
+// one launch, where the grid's way below takes six (about 3 us of host time
+// each, which small layers feel).
 template <int KPT>
 __global__ __launch_bounds__(1024) void k_sel_one(const uint64_t* __restrict__ keys, int64_t n, int64_t keep,
                                                   uint8_t* __restrict__ out) {
@@ -376,19 +376,14 @@ __global__ __launch_bounds__(1024) void k_sel_one(const uint64_t* __restrict__ k
         const int64_t i = threadIdx.x + 1024 * j;
         kv[j] = i < n ? keys[i] : 0;
     }
-    // key(i) for i = threadIdx.x + 1024 j comes from the registers; ties are
-    // ranked over contiguous runs, from memory
+    // ties are ranked over contiguous runs, from memory
     const SelCut c = sel_narrow(
-        [&](int64_t i) {
-            uint64_t k = 0;
-            if ((i & 1023) == int64_t(threadIdx.x)) {
+        [&](auto f) {
 #pragma unroll
-                for (int j = 0; j < KPT; ++j) k = (i >> 10) == j ? kv[j] : k;
-                return k;
-            }
-            return keys[i];
+            for (int j = 0; j < KPT; ++j)
+                if (threadIdx.x + 1024 * j < n) f(kv[j]);
         },
-        [](int64_t i) { return i; }, true, n, keep, 0, 0, sh);
+        [&](int64_t i) { return keys[i]; }, [](int64_t i) { return i; }, true, n, keep, 0, 0, sh);
 #pragma unroll
     for (int j = 0; j < KPT; ++j) {
         const int64_t i = threadIdx.x + 1024 * j;
@@ -471,9 +466,17 @@ __global__ __launch_bounds__(1024) void k_selw_cut(const uint64_t* __restrict__ 
     const int64_t count = s->count;
     const SelCut c =
         count <= kSelList
-            ? sel_narrow([&](int64_t i) { return s->key[i]; }, [&](int64_t i) { return int64_t(s->index[i]); }, false,
+            ? sel_narrow(
+                  [&](auto f) {
+                      for (int64_t i = threadIdx.x; i < count; i += 1024) f(s->key[i]);
+                  },
+                  [&](int64_t i) { return s->key[i]; }, [&](int64_t i) { return int64_t(s->index[i]); }, false,
                          count, r, prefix << 40, mask, sh)
-            : sel_narrow([&](int64_t i) { return keys[i]; }, [](int64_t i) { return i; }, true, n, r, prefix << 40,
+            : sel_narrow(
+                  [&](auto f) {
+                      for (int64_t i = threadIdx.x; i < n; i += 1024) f(keys[i]);
+                  },
+                  [&](int64_t i) { return keys[i]; }, [](int64_t i) { return i; }, true, n, r, prefix << 40,
                          mask, sh);
     if (threadIdx.x == 0) s->cut = c;
 }
