@@ -215,9 +215,9 @@ psc_status psc_conv3x3_fwd_strided(const psc_layer *layer, const psc_packed *pac
  * layers on the matrix cores: each call then decodes the packed weights into
  * the buffer and multiplies the dense tiles, fp16 values as they are and fp32
  * values in three bf16 parts whose sum is exact, with fp32 sums.  The buffer
- * holds nothing from one call to the next.  Calls on the same *packed may
- * share one buffer, also on several streams (each writes the same bytes);
- * calls on different ones that may overlap need one each. */
+ * holds nothing from one call to the next.  Calls on the same *packed, its
+ * arrays unchanged, may share one buffer, also on several streams (each writes
+ * the same bytes); any other calls that may overlap need one each. */
 psc_status psc_conv3x3_workspace(const psc_layer *layer, size_t *bytes);
 /* *out = 1 where psc_conv3x3_fwd_ws with algo 0 runs the matrix-core kernel
  * (host only, arguments validated as by psc_conv3x3_config). */

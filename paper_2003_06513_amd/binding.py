@@ -156,13 +156,21 @@ def _dev(t, name):
         raise ValueError("%s must be a device tensor" % name)
     if not t.is_contiguous():
         raise ValueError("%s must be contiguous" % name)
-    return ctypes.c_void_p(t.data_ptr()) if t.numel() else None
+    return t.data_ptr() if t.numel() else None
 
 
 def _stream(stream):
     torch = _torch()
     s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    return s.cuda_stream
+
+
+def _torch_stream(stream):
+    """``stream`` (None: the current one) as a torch stream."""
+    cuda = _torch().cuda
+    if stream is None:
+        return cuda.current_stream()
+    return stream if isinstance(stream, cuda.Stream) else cuda.ExternalStream(stream.cuda_stream)
 
 
 class Layer:
@@ -177,6 +185,7 @@ class Layer:
         for i, v in enumerate(masks[:MAX_PATTERNS]):
             self.c.masks[i] = v
         self.masks = np.array(masks, dtype=np.uint16)
+        self.sizes = (self.cout, self.cin, self.m, self.keep, self.dtype)
 
     cout = property(lambda self: self.c.cout)
     cin = property(lambda self: self.c.cin)
@@ -191,7 +200,7 @@ class Layer:
 class Packed:
     """Compressed weight storage held in device tensors (psc_packed)."""
 
-    work, work_bytes = None, 0      # also of an instance restored without them
+    _work = _layer = None           # also of an instance restored without them
 
     def __init__(self, layer: Layer, device="cuda"):
         torch = _torch()
@@ -203,12 +212,20 @@ class Packed:
         self.cin_idx = torch.empty(keep, dtype=torch.int32, device=device)
         self.pat_id = torch.empty(keep, dtype=torch.uint8, device=device)
         self.values = torch.empty(keep * 4, dtype=vdt, device=device)
-        # scratch of the convolution calls on this storage (None: they need
-        # none); every call writes it anew
-        b = ctypes.c_size_t(0)
-        _check(lib().psc_conv3x3_workspace(layer.ref(), ctypes.byref(b)), "psc_conv3x3_workspace")
-        self.work_bytes = int(b.value)
-        self.work = torch.empty(b.value, dtype=torch.uint8, device=device) if b.value else None
+        self._layer = layer
+
+    @property
+    def work(self):
+        """Scratch kept with the storage for its convolution calls, made when
+        first asked for (None: no call has a use for any).  Calls find it and
+        take none of their own, for callers that let nothing allocate (a
+        capture that torch knows nothing of).  Each call writes it anew: calls
+        that share it must not overlap, unless the storage is the same for
+        all of them."""
+        if self._work is None and self._layer is not None:
+            b = _workspace_bytes(self._layer)
+            self._work = _torch().empty(b, dtype=_torch().uint8, device=self.values.device) if b else None
+        return self._work
 
     def c(self) -> CPacked:
         # an empty tensor's address is 0: NULL
@@ -276,13 +293,62 @@ def unpack_dense(layer: Layer, packed: Packed, w_dense, stream=None):
                                   _stream(stream)), "psc_unpack_dense")
 
 
+def _workspace_bytes(layer: Layer) -> int:
+    b = ctypes.c_size_t(0)
+    _check(lib().psc_conv3x3_workspace(layer.ref(), ctypes.byref(b)), "psc_conv3x3_workspace")
+    return int(b.value)
+
+
+_SCRATCH: dict = {}     # _call_scratch by the sizes of a call, at most 4096 of them
+
+
+def _call_scratch(layer, dtype, n, h, w, pool, stride, where) -> int:
+    """The scratch bytes with which a call of algo 0 runs on the matrix cores;
+    0 where it runs the vector kernels in any case.  Kept by the sizes alone
+    (the library checks size and rule again)."""
+    key = (layer.sizes, dtype, n, h, w, pool, stride)
+    b = _SCRATCH.get(key)
+    if b is None:
+        takes = ctypes.c_int32(0)
+        _check(lib().psc_conv3x3_on_matrix_cores(layer.ref(), dtype, n, h, w, pool, stride, ctypes.byref(takes)),
+               where)
+        b = _workspace_bytes(layer) if takes.value else 0
+        if len(_SCRATCH) >= 4096:
+            _SCRATCH.clear()
+        _SCRATCH[key] = b
+    return b
+
+
+def _scratch(nbytes: int, stream):
+    """Device scratch of one call on ``stream``.  It comes from torch's pool of
+    that very stream and goes back when the call has been submitted, so that
+    whatever gets the memory next is ordered behind the call: no other call,
+    thread, stream or layer shares it, and an owner dropped early frees
+    nothing that the call still writes."""
+    torch = _torch()
+    if stream is None:
+        return torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    with torch.cuda.stream(_torch_stream(stream)):
+        return torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+
+
 def _conv(layer, packed, x, n, h, w, y, bias, relu, pool, stride, algo, stream, where):
-    """psc_conv3x3_fwd_ws with the scratch that the storage carries."""
-    cp, ws = packed.c(), packed.work
-    _check(lib().psc_conv3x3_fwd_ws(layer.c, cp, dtype_code(x), _dev(x, "x"), n, h, w, _dev(bias, "bias"),
-                                    int(bool(relu)), _dev(y, "y"), pool, stride, int(algo),
-                                    None if ws is None else ws.data_ptr(), packed.work_bytes, _stream(stream)),
-           where)
+    """psc_conv3x3_fwd_ws, with scratch where the call has a use for it."""
+    cp, dt, xp, bp, yp = packed.c(), dtype_code(x), _dev(x, "x"), _dev(bias, "bias"), _dev(y, "y")
+    ws, wp, nbytes = packed._work, None, 0
+    if ws is not None:
+        ws.record_stream(_torch_stream(stream))
+        wp, nbytes = ws.data_ptr(), ws.numel()
+    elif algo == 0:
+        nbytes = _call_scratch(layer, dt, n, h, w, pool, stride, where)
+        if nbytes:
+            try:
+                ws = _scratch(nbytes, stream)
+                wp = ws.data_ptr()
+            except _torch().cuda.OutOfMemoryError:
+                nbytes = 0                  # the vector kernels need none
+    _check(lib().psc_conv3x3_fwd_ws(layer.c, cp, dt, xp, n, h, w, bp, int(bool(relu)), yp, pool, stride, int(algo),
+                                    wp, nbytes, _stream(stream)), where)
 
 
 def conv3x3_fwd(layer: Layer, packed: Packed, x, y, bias=None, relu: bool = False, algo: int = 0,
