@@ -370,7 +370,9 @@ psc_status psc_dense3x3_fwd(int32_t dtype, const void *d_x, int32_t n, int32_t c
 /* The same with a scratch buffer of the caller's, at least
  * psc_dense3x3_fwd_workspace bytes and 256-byte aligned (NULL: exactly that
  * call).  With it fp32 layers of at least 16 input channels and 32 filters run
- * on the 16-bit matrix cores, each value in three bf16 parts whose sum is exact. */
+ * on the 16-bit matrix cores, each value in three bf16 parts whose sum is exact.
+ * The buffer holds nothing from one call to the next; calls that may overlap
+ * need one each. */
 psc_status psc_dense3x3_fwd_workspace(int32_t dtype, int32_t cin, int32_t cout, size_t *bytes);
 psc_status psc_dense3x3_fwd_ws(int32_t dtype, const void *d_x, int32_t n, int32_t cin,
                                int32_t h, int32_t w, const void *d_w, int32_t cout,

@@ -324,29 +324,28 @@ def _scratch(nbytes: int, stream):
     that very stream and goes back when the call has been submitted, so that
     whatever gets the memory next is ordered behind the call: no other call,
     thread, stream or layer shares it, and an owner dropped early frees
-    nothing that the call still writes."""
+    nothing that the call still writes.  None where there is no room: the
+    kernels that need none run instead."""
     torch = _torch()
-    if stream is None:
-        return torch.empty(nbytes, dtype=torch.uint8, device="cuda")
-    with torch.cuda.stream(_torch_stream(stream)):
-        return torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    try:
+        if stream is None:
+            return torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        with torch.cuda.stream(_torch_stream(stream)):
+            return torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    except torch.cuda.OutOfMemoryError:
+        return None
 
 
 def _conv(layer, packed, x, n, h, w, y, bias, relu, pool, stride, algo, stream, where):
     """psc_conv3x3_fwd_ws, with scratch where the call has a use for it."""
     cp, dt, xp, bp, yp = packed.c(), dtype_code(x), _dev(x, "x"), _dev(bias, "bias"), _dev(y, "y")
-    ws, wp, nbytes = packed._work, None, 0
+    ws = packed._work
     if ws is not None:
         ws.record_stream(_torch_stream(stream))
-        wp, nbytes = ws.data_ptr(), ws.numel()
     elif algo == 0:
         nbytes = _call_scratch(layer, dt, n, h, w, pool, stride, where)
-        if nbytes:
-            try:
-                ws = _scratch(nbytes, stream)
-                wp = ws.data_ptr()
-            except _torch().cuda.OutOfMemoryError:
-                nbytes = 0                  # the vector kernels need none
+        ws = _scratch(nbytes, stream) if nbytes else None
+    wp, nbytes = (None, 0) if ws is None else (ws.data_ptr(), ws.numel())
     _check(lib().psc_conv3x3_fwd_ws(layer.c, cp, dt, xp, n, h, w, bp, int(bool(relu)), yp, pool, stride, int(algo),
                                     wp, nbytes, _stream(stream)), where)
 
@@ -556,6 +555,8 @@ class AdmmLayer:
         self.energy = torch.empty(K, dtype=torch.float64, device=w0.device)
         self.keep_mask = torch.empty(K, dtype=torch.uint8, device=w0.device)
         self.ws_sel = None if noalloc else workspace(self.layer, PSC_OP_SELECT, w0.device)
+        # the iterations' scratch: target() may run beside them, on another
+        # stream, and takes its own
         self.ws_dense = dense3x3_fwd_workspace(PSC_F32, cin, cout, w0.device)
         self.ws_res = torch.empty(ADMM_RESIDUAL_WS_BYTES, dtype=torch.uint8, device=w0.device)
         self.loss = torch.zeros(1, dtype=torch.float64, device=w0.device)
@@ -573,7 +574,8 @@ class AdmmLayer:
         """X' = relu(W0 X + b0): the pre-trained layer's output."""
         n, _, h, w = x.shape
         out = out if out is not None else self._buf("target", (n, self.layer.cout, h, w))
-        dense3x3_fwd(x, self.w0, out, bias=self.b0, relu=True, stream=stream, ws=self.ws_dense)
+        ws = None if self.ws_dense is None else _scratch(self.ws_dense.numel(), stream)
+        dense3x3_fwd(x, self.w0, out, bias=self.b0, relu=True, stream=stream, ws=ws)
         return out
 
     def iteration(self, x, target, rho: float, scale: float, stream=None):

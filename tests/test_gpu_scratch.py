@@ -91,3 +91,47 @@ def test_kept_scratch_and_capture(dtype):
     run()
     torch.cuda.synchronize()
     assert torch.equal(y, want)
+
+
+def test_admm_target_and_iteration_take_different_scratch(monkeypatch):
+    """target() on the next batch may run beside an iteration: host only, with
+    the library's calls left out."""
+    torch = torch_mod()
+    used = []
+
+    def fwd(x, w, y, bias=None, relu=False, stream=None, ws=None):
+        used.append(ws.data_ptr())
+        if len(used) == 2:
+            raise StopIteration
+
+    monkeypatch.setattr(B, "dense3x3_fwd", fwd)
+    monkeypatch.setattr(B, "_scratch", lambda b, stream: torch.empty(b, dtype=torch.uint8), raising=False)
+    st = B.AdmmLayer(torch.zeros(32, 16, 3, 3), torch.zeros(32), [23, 282], 200)
+    x = torch.zeros(1, 16, 4, 4)
+    t = st.target(x)
+    with pytest.raises(StopIteration):
+        st.iteration(x, t, 1e-3, 1.0)
+    assert used[0] != used[1]
+
+
+@pytest.mark.gpu
+def test_admm_target_beside_an_iteration():
+    _need_gpu()
+    torch = torch_mod()
+    wt = inputs.he_weights(41, 64, 64)
+    st = B.AdmmLayer(dev(wt), dev(inputs.bias_vector(42, 64)), B.select_library(wt, 8), 2000)
+    x = dev(inputs.normal_activations(43, (32, 64, 32, 32)))
+    note("scratch, target beside an iteration")
+    target = st.target(x)
+    want = target.clone()
+    st.iteration(x, target, 1e-2, 1e-3)
+    st.w.mul_(3)                                # far from W0
+    torch.cuda.synchronize()
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    outs = [torch.empty_like(target) for _ in range(20)]
+    torch.cuda.synchronize()
+    for out in outs:
+        st.iteration(x, target, 1e-2, 1e-3, stream=s1)
+        st.target(x, out=out, stream=s2)
+    torch.cuda.synchronize()
+    assert all(torch.equal(out, want) for out in outs)
