@@ -602,7 +602,15 @@ __global__ __launch_bounds__(256) void k_pack_seg(const int32_t* __restrict__ cn
     seg[int64_t(i) * (m + 1) + m] = fptr[i + 1];
 }
 
-// Scatter of one reordered filter per wave: a kernel's slot is the start of
+// What the lanes of a wave did to memory before it happens before what they do
+// after it.
+__device__ __forceinline__ void wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
+// Scatter of one reordered filter per block: a kernel's slot is the start of
 // its pattern's segment + kept kernels of that pattern at lower ci.
 template <typename B>
 __global__ __launch_bounds__(256) void k_pack_scatter(const B* __restrict__ w,
@@ -645,15 +653,19 @@ __global__ __launch_bounds__(256) void k_pack_scatter(const B* __restrict__ w,
         const int64_t k = int64_t(f) * cin + ci;
         const int pp = ci < hi ? pat[k] : kMaxPatterns;
         const bool kept = ci < hi && keep[k] && pp < m;
-        // the lanes of one pattern at a time: their first lane's cursor, in
-        // lane order (a wave's LDS accesses are served in order)
+        // the lanes of one pattern at a time, from the pattern's cursor in
+        // lane order; the wave's barriers order the lanes' reads of a cursor
+        // against the one lane's update of it (no instruction waits for them:
+        // a wave's LDS accesses are served in order)
         uint64_t todo = __ballot(kept);
         int pos = -1;
         while (todo) {
             const int p = __shfl(pp, __builtin_ctzll(todo));
             const uint64_t b = __ballot(kept && pp == p);
             if (kept && pp == p) pos = cur[wave][p] + __popcll(b & ((uint64_t(1) << lane) - 1));
+            wave_order();
             if (lane == __builtin_ctzll(b)) cur[wave][p] += __popcll(b);
+            wave_order();
             todo &= ~b;
         }
         if (kept && pos >= 0 && pos < n_keep) {   // a keep mask with too many ones writes nothing past the arrays
