@@ -236,6 +236,9 @@ __global__ __launch_bounds__(256) void k_sel_mark(const uint64_t* __restrict__ k
 // passes of 8 bits: 4096 kernels 37 -> 9 us in one block, 262144 kernels 19
 // launches and 105 us -> 6 and 25.
 constexpr int kSelBins = 2048;
+// Lines: one block 38 us at 16384 tied keys where the grid takes 40 (random 23,
+// 22); above 2^20 kernels (4096 a block of pass 0) the radix passes stay, 132 us
+// there.
 constexpr int64_t kSelOneBlockMax = 16384, kSelFastMax = int64_t(1) << 20;
 
 struct SelCut {
@@ -394,18 +397,39 @@ __global__ __launch_bounds__(1024) void k_sel_one(const uint64_t* __restrict__ k
 // More keys: two histograms of 12 bits (sign and exponent, then the top of
 // the mantissa) over the whole grid, the keys of the bin that is left in a
 // list, T and cut from the list in one block, then the mask: 6 launches.  Each
-// block takes the digit of the pass before from its histogram.  A list that
-// overflows (thousands of equal leading bits) makes the one block go over all
-// the keys instead.
-constexpr int kSelWide = 4096, kSelList = 2560;
+// block takes the digit of the pass before from its histogram.  Where the bin
+// holds more keys than the list (thousands of equal leading bits: weights
+// already pruned, or of few values), pass 2 goes on over the whole grid in
+// rounds of 10 bits (one, where the keys of the bin are all equal) and then
+// ranks the ties, instead of the list.
+// Measured (half kept; 8 passes of 8 bits first, then one block going over all
+// the keys, then the rounds, us): 262144 kernels random 92, 24, 24; all equal
+// 147, 252, 53; 70 % zeros 142, 250, 53; eight values 141, 244, 52; equal in 32
+// leading bits 136, 365, 93; 1048576 kernels random 133, 31, 31; all equal 247,
+// 1211, 92; equal in 32 bits 235, 2257, 163.
+constexpr int kSelWide = 4096, kSelList = 2560, kSelRounds = 4, kSelChunks = 32;
+struct SelStage {                                // each counter in a line of its own
+    uint32_t claim, pad[63], done, pad2[63];
+};
+struct SelTail {                                 // of pass 2 without a list
+    uint32_t hist[kSelRounds][1024];
+    uint32_t ties[kSelChunks];                   // keys equal to T, by chunk
+    unsigned long long ones, zeros;              // bits set, and clear, in some key of the bin
+    SelStage stage[kSelRounds + 2];
+};
 struct SelWide {
     uint32_t hist[2][kSelWide];
     uint32_t count;
     uint32_t pad[63];
     SelCut cut;
     uint64_t pad2[30];
-    uint64_t key[kSelList];
-    uint32_t index[kSelList];
+    union {
+        struct {
+            uint64_t key[kSelList];
+            uint32_t index[kSelList];
+        };
+        SelTail tail;                            // zeroed by pass 1
+    };
 };
 static_assert(sizeof(SelWide) <= 64 * 1024, "the scratch of psc_select_noalloc");
 
@@ -414,12 +438,173 @@ __global__ __launch_bounds__(1024) void k_selw_clear(SelWide* __restrict__ s) {
     if (threadIdx.x == 0) s->count = 0;
 }
 
-// Pass 0 or 1, or (pass 2) the list of the keys that match both digits.
+// One more in `bin` of each active lane's; one addition for the wave where
+// they are all the same bin (ties), which LDS would serve one by one.
+__device__ __forceinline__ void hist_add(uint32_t* h, uint32_t bin) {
+    const uint64_t on = __ballot(1);
+    const int first = __builtin_ctzll(on);
+    if (__ballot(bin == uint32_t(__shfl(int(bin), first))) == on) {
+        if (int(threadIdx.x & 63) == first) atomicAdd(&h[bin], uint32_t(__popcll(on)));
+    } else {
+        atomicAdd(&h[bin], 1u);
+    }
+}
+
+template <typename T>
+__device__ __forceinline__ T load_agent(const T* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The next item of a stage of k_selw_pass<2>'s rounds, in every thread of the
+// block.
+__device__ __forceinline__ uint32_t sel_claim(SelTail* tl, int stage, uint32_t* item) {
+    __syncthreads();                             // every thread has read the last one
+    if (threadIdx.x == 0) *item = atomicAdd(&tl->stage[stage].claim, 1u);
+    __syncthreads();
+    return *item;
+}
+
+// What the block wrote for an item is seen by every block that waits for the
+// stage.
+__device__ __forceinline__ void sel_finish(SelTail* tl, int stage) {
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0)
+        __hip_atomic_fetch_add(&tl->stage[stage].done, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Until all items of a stage are done.  A block comes here only when every
+// item is claimed, and a block that has claimed one finishes it without
+// waiting for any other: the wait ends however few blocks run at a time.
+__device__ __forceinline__ void sel_wait(const SelTail* tl, int stage, uint32_t items) {
+    if (threadIdx.x == 0) {
+        while (load_agent(&tl->stage[stage].done) < items) __builtin_amdgcn_s_sleep(4);
+        __threadfence();
+    }
+    __syncthreads();
+}
+
+// Pass 2 without a list: T and cut of the r largest of the keys that match
+// `prefix` in their upper 24 bits.  The keys are cut into at most kSelChunks
+// chunks, which the first as many blocks take as they come to them (a stage
+// costs about 0.3 us a block in traffic on its counters: equal in 32 leading
+// bits, 262144 kernels, 93 us in 32 chunks, 130 in 64).
+__device__ __forceinline__ void sel_rounds(const uint64_t* __restrict__ keys, int64_t n, int64_t r, uint64_t prefix,
+                                           SelWide* s, uint32_t* lh, SelShared& sh) {
+    __shared__ uint32_t item;
+    SelTail* const tl = &s->tail;
+    const uint32_t chunks = gridDim.x < kSelChunks ? gridDim.x : kSelChunks;
+    if (blockIdx.x >= chunks) return;
+    const int64_t per = (n + chunks - 1) / chunks;
+    const int t = threadIdx.x;
+    bool all = false;                            // every key that is left is kept
+    int round = 0;
+    for (; round < kSelRounds && !all; ++round) {
+        const int shift = 10 * (kSelRounds - 1 - round), up = shift + 10;
+        for (uint32_t c; (c = sel_claim(tl, round, &item)) < chunks;) {
+            lh[t] = 0;
+            __syncthreads();
+            const int64_t end = min<int64_t>(n, (c + 1) * per);
+            unsigned long long ones = 0, zeros = 0;
+            for (int64_t i = c * per + t; i < end; i += 1024) {
+                const uint64_t k = keys[i];
+                if (k >> up != prefix) continue;
+                hist_add(lh, (k >> shift) & 1023);
+                ones |= k;
+                zeros |= ~k;
+            }
+            __syncthreads();
+            if (lh[t]) atomicAdd(&tl->hist[round][t], lh[t]);
+            if (round == 0) {
+                for (int off = 32; off > 0; off >>= 1) {
+                    ones |= __shfl_xor(ones, off);
+                    zeros |= __shfl_xor(zeros, off);
+                }
+                if ((t & 63) == 0) sh.w_and[t >> 6] = ones, sh.w_or[t >> 6] = zeros;
+                __syncthreads();
+                if (t == 0) {
+                    for (int w = 1; w < 16; ++w) ones |= sh.w_and[w], zeros |= sh.w_or[w];
+                    atomicOr(&tl->ones, ones);
+                    atomicOr(&tl->zeros, zeros);
+                }
+            }
+            sel_finish(tl, round);
+        }
+        sel_wait(tl, round, chunks);
+        if (round == 0) {                        // all equal: no further digit
+            const uint64_t ones = load_agent(&tl->ones);
+            if ((ones & load_agent(&tl->zeros)) == 0) {
+                prefix = ones;
+                break;
+            }
+        }
+        lh[t] = load_agent(&tl->hist[round][t]);
+        __syncthreads();
+        sel_bin(lh, 1024, r, sh);
+        r -= sh.above;
+        prefix = prefix << 10 | uint64_t(sh.digit);
+        all = int64_t(lh[sh.digit]) == r;
+        __syncthreads();                         // every thread has read sh and lh
+    }
+    if (all) {                                   // T is the lower end of the bin
+        if (sel_claim(tl, kSelRounds + 1, &item) == 0 && t == 0)
+            s->cut = SelCut{prefix << (10 * (kSelRounds - round)), INT64_MAX};
+        return;
+    }
+    // the r-th lowest index of the keys equal to T: by chunk, then inside one
+    const uint64_t T = prefix;
+    for (uint32_t c; (c = sel_claim(tl, kSelRounds, &item)) < chunks;) {
+        const int64_t end = min<int64_t>(n, (c + 1) * per);
+        int own = 0;
+        for (int64_t i = c * per + t; i < end; i += 1024) own += keys[i] == T;
+        for (int off = 32; off > 0; off >>= 1) own += __shfl_xor(own, off);
+        if ((t & 63) == 0) sh.wsum[t >> 6] = own;
+        __syncthreads();
+        if (t == 0) {
+            uint32_t sum = 0;
+            for (int w = 0; w < 16; ++w) sum += sh.wsum[w];
+            __hip_atomic_store(&tl->ties[c], sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        sel_finish(tl, kSelRounds);
+    }
+    sel_wait(tl, kSelRounds, chunks);
+    if (sel_claim(tl, kSelRounds + 1, &item) != 0) return;
+    // inclusive sums of `part` over the block
+    auto scan = [&](uint32_t v) {
+        sh.part[t] = v;
+        __syncthreads();
+        for (int off = 1; off < 1024; off <<= 1) {
+            const uint32_t b = t >= off ? sh.part[t - off] : 0u;
+            __syncthreads();
+            sh.part[t] += b;
+            __syncthreads();
+        }
+        return sh.part[t];
+    };
+    const uint32_t v = t < int(chunks) ? load_agent(&tl->ties[t]) : 0u, inc = scan(v);
+    if (int64_t(inc) >= r && int64_t(inc - v) < r) {     // one thread
+        sh.digit = t;
+        sh.above = inc - v;
+    }
+    __syncthreads();
+    const int64_t beg = sh.digit * per, end = min<int64_t>(n, beg + per), quarter = (per + 1023) / 1024;
+    r -= sh.above;
+    const int64_t lo = min<int64_t>(end, beg + t * quarter), hi = min<int64_t>(end, lo + quarter);
+    uint32_t own = 0;
+    for (int64_t i = lo; i < hi; ++i) own += keys[i] == T;
+    int64_t rank = int64_t(scan(own)) - own;
+    if (rank < r && rank + own >= r)                     // one thread
+        for (int64_t i = lo; i < hi; ++i)
+            if (keys[i] == T && ++rank == r) s->cut = SelCut{T, i};
+}
+
+// Pass 0 or 1, or (pass 2) the list of the keys that match both digits, or the
+// rounds.
 template <int PASS>
 __global__ __launch_bounds__(1024) void k_selw_pass(const uint64_t* __restrict__ keys, int64_t n, int64_t keep,
-                                                    SelWide* __restrict__ s) {
+                                                    SelWide* s) {
     __shared__ SelShared sh;
-    __shared__ uint32_t lh[PASS < 2 ? kSelWide : 1];
+    __shared__ uint32_t lh[PASS < 2 ? kSelWide : 1024];
     int64_t r = keep;
     uint64_t prefix = 0;
 #pragma unroll
@@ -431,14 +616,19 @@ __global__ __launch_bounds__(1024) void k_selw_pass(const uint64_t* __restrict__
     }
     if (PASS < 2) {
         for (int b = threadIdx.x; b < kSelWide; b += 1024) lh[b] = 0;
+        if (PASS == 1 && blockIdx.x == 0)
+            for (int b = threadIdx.x; b < int(sizeof(SelTail) / 4); b += 1024) reinterpret_cast<uint32_t*>(&s->tail)[b] = 0;
         __syncthreads();
+    } else if (s->hist[1][prefix & 4095] > kSelList) {
+        sel_rounds(keys, n, r, prefix, s, lh, sh);
+        return;
     }
     for (int64_t i = int64_t(blockIdx.x) * 1024 + threadIdx.x; i < n; i += int64_t(gridDim.x) * 1024) {
         const uint64_t k = keys[i];
         if (PASS == 0) {
             atomicAdd(&lh[k >> 52], 1u);
         } else if (PASS == 1) {
-            if (k >> 52 == prefix) atomicAdd(&lh[(k >> 40) & 4095], 1u);
+            if (k >> 52 == prefix) hist_add(lh, (k >> 40) & 4095);
         } else if (k >> 40 == prefix) {
             const uint32_t at = atomicAdd(&s->count, 1u);
             if (at < kSelList) s->key[at] = k, s->index[at] = uint32_t(i);
@@ -451,8 +641,7 @@ __global__ __launch_bounds__(1024) void k_selw_pass(const uint64_t* __restrict__
     }
 }
 
-__global__ __launch_bounds__(1024) void k_selw_cut(const uint64_t* __restrict__ keys, int64_t n, int64_t keep,
-                                                   SelWide* __restrict__ s) {
+__global__ __launch_bounds__(1024) void k_selw_cut(int64_t keep, SelWide* __restrict__ s) {
     __shared__ SelShared sh;
     int64_t r = keep;
     uint64_t prefix = 0;
@@ -462,22 +651,14 @@ __global__ __launch_bounds__(1024) void k_selw_cut(const uint64_t* __restrict__ 
         prefix = prefix << 12 | uint64_t(sh.digit);
         __syncthreads();
     }
-    const uint64_t mask = ~((uint64_t(1) << 40) - 1);
+    if (s->hist[1][prefix & 4095] > kSelList) return;    // pass 2 has written it
     const int64_t count = s->count;
-    const SelCut c =
-        count <= kSelList
-            ? sel_narrow(
-                  [&](auto f) {
-                      for (int64_t i = threadIdx.x; i < count; i += 1024) f(s->key[i]);
-                  },
-                  [&](int64_t i) { return s->key[i]; }, [&](int64_t i) { return int64_t(s->index[i]); }, false,
-                         count, r, prefix << 40, mask, sh)
-            : sel_narrow(
-                  [&](auto f) {
-                      for (int64_t i = threadIdx.x; i < n; i += 1024) f(keys[i]);
-                  },
-                  [&](int64_t i) { return keys[i]; }, [](int64_t i) { return i; }, true, n, r, prefix << 40,
-                         mask, sh);
+    const SelCut c = sel_narrow(
+        [&](auto f) {
+            for (int64_t i = threadIdx.x; i < count; i += 1024) f(s->key[i]);
+        },
+        [&](int64_t i) { return s->key[i]; }, [&](int64_t i) { return int64_t(s->index[i]); }, false, count, r,
+        prefix << 40, ~((uint64_t(1) << 40) - 1), sh);
     if (threadIdx.x == 0) s->cut = c;
 }
 
@@ -762,7 +943,7 @@ hipError_t launch_select(int64_t n, int64_t keep, const double* energy, uint8_t*
         hipLaunchKernelGGL(k_selw_pass<0>, g, dim3(1024), 0, stream, k, n, keep, s);
         hipLaunchKernelGGL(k_selw_pass<1>, g, dim3(1024), 0, stream, k, n, keep, s);
         hipLaunchKernelGGL(k_selw_pass<2>, g, dim3(1024), 0, stream, k, n, keep, s);
-        hipLaunchKernelGGL(k_selw_cut, dim3(1), dim3(1024), 0, stream, k, n, keep, s);
+        hipLaunchKernelGGL(k_selw_cut, dim3(1), dim3(1024), 0, stream, keep, s);
         hipLaunchKernelGGL(k_selw_mark, dim3(unsigned(grid_for(n, 256, 2048))), dim3(256), 0, stream, k, n, s, keep_out);
         return hipGetLastError();
     }

@@ -58,3 +58,32 @@ def test_keep_mask(shape, kind):
         B.select_noalloc(L, ed, got.fill_(7))
         torch.cuda.synchronize()
         assert np.array_equal(got.cpu().numpy(), oracle.select(e, keep))
+
+
+@pytest.mark.parametrize("keep", [1, 12000, 30000, 49151])
+def test_ties_over_the_grid(keep):
+    """More equal leading bits than the list holds, in every round and at
+    every place where the rounds can end; repeated, and from two streams (each
+    with its workspace) at a time."""
+    torch = torch_mod()
+    k = 48 * 1024 + 13                      # 13 chunks, the last one short
+    rng = np.random.default_rng(keep)
+    step = lambda b: 1.0 + rng.integers(0, 3, k) * 2.0 ** -b
+    kinds = {"round%d" % i: step(b) for i, b in enumerate((22, 32, 42, 52))}
+    kinds["mixed"] = np.where(rng.random(k) < 0.5, 1.0, 1.0 + rng.integers(0, 1 << 12, k) * 2.0 ** -52)
+    kinds["small"] = np.where(rng.random(k) < 0.9, 0.0, 5e-324 * rng.integers(1, 9, k))
+    L = B.Layer(1, k, [23, 282], keep, B.PSC_F32)
+    for kind, e in kinds.items():
+        want = oracle.select(e, keep)
+        ed = dev(e)
+        streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+        ws = [B.workspace(L, B.PSC_OP_SELECT).fill_(255) for _ in streams]
+        got = [torch.full((k,), 7, dtype=torch.uint8, device="cuda") for _ in streams]
+        note("select rounds keep %d %s" % (keep, kind))
+        torch.cuda.synchronize()
+        for _ in range(5):
+            for s, w, g in zip(streams, ws, got):
+                B.select(L, ed, g, w, stream=s)
+        torch.cuda.synchronize()
+        for g in got:
+            assert np.array_equal(g.cpu().numpy(), want), kind
