@@ -328,7 +328,8 @@ __global__ __launch_bounds__(kT, 2) void k_conv_split(const float* __restrict__ 
     for (int t = 0; t < NI; ++t)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const uint32_t u = __builtin_bit_cast(uint32_t, acc[t][r]) << 1;
+            const float v = acc[t][r];                   // a bit cast of the element itself gives element 0
+            const uint32_t u = __builtin_bit_cast(uint32_t, v) << 1;
             // 2 * 0x7f800000, and 2 * the bits of 2^-90 less one
             again |= u >= 0xff000000u || u - 1 < 2u * 0x12800000u - 1;
         }

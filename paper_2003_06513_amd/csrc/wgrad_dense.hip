@@ -273,7 +273,8 @@ __global__ __launch_bounds__(256, 2) void k_wgrad_mfma(
 #pragma unroll
         for (int r = 0; r < 16; ++r)
             if (owns(q, r)) {
-                const uint32_t u = __builtin_bit_cast(uint32_t, acc[q][r]) << 1;
+                const float v = acc[q][r];               // a bit cast of the element itself gives element 0
+                const uint32_t u = __builtin_bit_cast(uint32_t, v) << 1;
                 // 2 * 0x7f800000, and 2 * the bits of 2^-90 less one
                 again |= u >= 0xff000000u || (DT == DT_F32 && u - 1 < 2u * 0x12800000u - 1);
             }

@@ -116,3 +116,73 @@ def test_values_that_bf16_parts_cannot_hold(scale):
     lim = 2 * gamma(max_terms(packed)) * 8 * (float(np.sqrt(max_terms(packed))) * scale if scale != 1.0 else 1.0)
     d = (y[ok] - z[ok]).abs()
     assert float((d / z[ok].abs().clamp(min=scale)).max()) <= max(lim, 1e-4 if scale == 1.0 else lim / scale)
+
+
+def _by_definition(x, w):
+    """Sums over the taps inside the image alone (nothing is multiplied by the
+    padding), float64."""
+    n, c, h, wd = x.shape
+    y = np.zeros((n, w.shape[0], h, wd))
+    for q in range(9):
+        r, s = q // 3 - 1, q % 3 - 1
+        i0, i1, j0, j1 = max(0, -r), min(h, h - r), max(0, -s), min(wd, wd - s)
+        xs = x[:, None, :, i0 + r:i1 + r, j0 + s:j1 + s].astype(np.float64)
+        y[:, :, i0:i1, j0:j1] += (xs * w[None, :, :, q // 3, q % 3, None, None].astype(np.float64)).sum(2)
+    return y
+
+
+@pytest.mark.parametrize("filters", [(7,), (1, 2, 3), (21, 30), (64,)], ids=str)
+@pytest.mark.parametrize("kind", ["weight", "x", "tiny"])
+def test_dense_values_that_bf16_parts_cannot_hold(kind, filters):
+    """Any filter of a block alone brings the block to the fp32 sums: an
+    infinite weight, an infinite input beside zero columns, and weights whose
+    parts leave the range of bf16."""
+    torch = torch_mod()
+    n, cin, cout, h, w = DENSE[2]
+    x, wt = inputs.normal_activations(1, (n, cin, h, w)), inputs.he_weights(2, cout, cin)
+    for f in filters:
+        if kind == "weight":
+            wt[f, 5, 0, 0], wt[f, 6, 2, 2] = np.inf, -3e38
+        elif kind == "tiny":
+            wt[f] *= np.float32(2.0 ** -120)
+        else:
+            wt[f, 9] = 0.0                          # 0 * inf
+    if kind == "x":
+        x[0, 9, 3, 3], x[1, 2, 0, 0], x[0, 4, 6, 6], x[1, 0, 2, 6] = np.inf, -np.inf, np.nan, 3.3e38
+    y = torch.empty((n, cout, h, w), device="cuda")
+    note("split dense %s %s" % (kind, filters))
+    B.dense3x3_fwd(dev(x), dev(wt), y, ws=B.dense3x3_fwd_workspace(B.PSC_F32, cin, cout))
+    got = y.cpu().numpy().astype(np.float64)
+    with np.errstate(all="ignore"):
+        want = _by_definition(x, wt)
+        want[np.abs(want) > np.finfo(np.float32).max] *= np.inf
+        fin = lambda a: np.where(np.isfinite(a), np.abs(a.astype(np.float64)), 0)
+        mag = _by_definition(fin(x), fin(wt))
+    sure = mag < 3e38                               # a sum near the largest number may differ in kind
+    assert np.array_equal(np.isnan(got)[sure], np.isnan(want)[sure])
+    assert np.array_equal(np.isinf(got)[sure], np.isinf(want)[sure])
+    ok = sure & np.isfinite(want)
+    assert (np.abs(got[ok] - want[ok]) <= gamma(9 * cin + 1) * mag[ok] + 2 * 9 * cin * 2.0 ** -149).all()
+
+
+def test_sparse_filters_that_bf16_parts_cannot_hold():
+    """The same for packed weights, filter by filter, against the
+    one-output-per-lane kernel."""
+    torch = torch_mod()
+    n, cin, cout, h, w, drop, stride, m = SPARSE[3]
+    x = dev(inputs.normal_activations(6, (n, cin, h, w)))
+    for f in (0, 1, 6, 11, 35, 63):
+        wt = inputs.he_weights(5, cout, cin)
+        masks = B.select_library(wt, m)
+        wt[f] *= np.float32(2.0 ** -120)
+        prep, packed = prepared_case(wt, masks, inputs.keep_after_drop(cout * cin, drop))
+        assert B.conv3x3_on_matrix_cores(prep.layer, B.PSC_F32, n, h, w, False, stride)
+        y = torch.empty((n, cout, (h - 1) // stride + 1, (w - 1) // stride + 1), device="cuda")
+        z = torch.empty_like(y)
+        note("split sparse tiny filter %d" % f)
+        B.conv3x3_fwd_strided(prep.layer, prep.packed, x, y, stride)
+        B.conv3x3_fwd_strided(prep.layer, prep.packed, x, z, stride, algo=1)
+        torch.cuda.synchronize()
+        # two fp32 sums of the same 4 cin products and outputs of one size
+        top = float(z[:, f].abs().max())
+        assert top > 0 and float((y[:, f] - z[:, f]).abs().max()) <= 2 * gamma(4 * cin) * top + 8 * cin * 2.0 ** -149

@@ -118,3 +118,53 @@ def test_values_that_bf16_parts_cannot_hold(scale):
     ok = np.isfinite(want) & ~big
     mag = _wgrad(np.where(np.isfinite(x), np.abs(x), 0), np.where(np.isfinite(g), np.abs(g), 0))
     assert (np.abs(got[ok] - want[ok]) <= gamma(6 * n * h * w) * mag[ok] + 300 * 2.0 ** -149).all()
+
+
+# n, cin, cout, h, w: 32-wide blocks (rows whole and in parts, ragged), and
+# 64-wide ones (at least 64 of them, and 4096 pixels)
+NON_FINITE = [(5, 33, 70, 9, 13), (2, 48, 36, 5, 130), (64, 512, 500, 8, 8)]
+
+
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+@pytest.mark.parametrize("shape", NON_FINITE, ids=["x".join(map(str, s)) for s in NON_FINITE])
+def test_masked_non_finite(shape, dtype):
+    """Infinities and NaNs, also at the edges of the image beside the zero
+    padding, reach the entries that read them and no others; every kernel is
+    kept, so every call takes the matrix cores."""
+    torch = torch_mod()
+    n, cin, cout, h, w = shape
+    x = inputs.normal_activations(5, (n, cin, h, w), dtype)
+    g = inputs.normal_activations(6, (n, cout, h, w), dtype)
+    x[0, 1, 0, 0], x[n - 1, 2, h - 1, w - 1], x[1, 3, 2, w - 1] = np.inf, -np.inf, np.nan
+    g[1, 4, h - 1, 0], g[0, 7, 0, w - 1], g[1, 8, 2, 3] = np.inf, -np.inf, np.nan
+    wt = inputs.he_weights(7, cout, cin, dtype)
+    masks = B.select_library(wt, 8)
+    prep = B.prepare(dev(wt), masks, cout * cin)
+    dv = torch.empty(4 * cout * cin, device="cuda")
+    note("masked wgrad non-finite %s %s" % (shape, np.dtype(dtype).name))
+    ws = B.conv3x3_bwd_weight(prep.layer, prep.packed, dev(x), dev(g), dv)
+    assert ws.numel() >= 36 * cout * cin        # a slot of the dense gradient
+    pk = prep.packed.to_host()
+    pos = np.repeat(np.arange(cout), np.diff(pk["filter_ptr"]))
+    bits = np.array([[b for b in range(9) if (int(c) >> b) & 1] for c in masks])[pk["pat_id"]]
+    filters = [0, 4, 7, 8, cout - 1]
+    got = np.zeros((cout, cin, 9))
+    kept = np.zeros((cout, cin, 9), bool)
+    at = (pk["filter_perm"][pos][:, None], pk["cin_idx"][:, None], bits)
+    got[at], kept[at] = dv.cpu().numpy().reshape(-1, 4), True
+    fin = lambda a: np.where(np.isfinite(a), np.abs(a.astype(np.float64)), 0)
+    mag = _wgrad(fin(x), fin(g))
+    for f in filters:
+        want = np.empty((cin, 9))
+        with np.errstate(all="ignore"):
+            for q in range(9):
+                r, s = q // 3 - 1, q % 3 - 1
+                i0, i1, j0, j1 = max(0, -r), min(h, h - r), max(0, -s), min(w, w - s)
+                xs = x[:, :, i0 + r:i1 + r, j0 + s:j1 + s].astype(np.float64)
+                want[:, q] = (g[:, f, None, i0:i1, j0:j1].astype(np.float64) * xs).sum((0, 2, 3))
+        k = kept[f]
+        assert np.array_equal(np.isnan(got[f][k]), np.isnan(want[k]))
+        assert np.array_equal(np.isinf(got[f][k]), np.isinf(want[k]))
+        ok = k & np.isfinite(want)
+        assert f or ok.any()
+        assert (np.abs(got[f][ok] - want[ok]) <= gamma(6 * n * h * w) * mag[f][ok] + 1e-37).all()
