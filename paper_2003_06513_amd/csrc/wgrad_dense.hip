@@ -58,9 +58,21 @@ __device__ __forceinline__ f16v mfma(const u4& a, const u4& b, const f16v& c, In
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(b8, a), __builtin_bit_cast(b8, b), c, 0, 0, 0);
 }
 
-// 8 columns of a row: fp16 as they are, fp32 split into three bf16 parts;
-// the columns from `left` on read zero.
+// 8 columns of a row: fp16 as they are, fp32 split into three bf16 parts
+// (raw_unit: as they are, in the first two); the columns from `left` on read
+// zero.
 template <int DT> struct Raw { uint32_t w[DT == DT_F32 ? 8 : 4]; };
+
+template <int DT>
+__device__ __forceinline__ void raw_unit(Raw<DT>& v, int left, u4 (&parts)[DT == DT_F32 ? 3 : 1]) {
+#pragma unroll
+    for (int k = 0; k < 8 && DT == DT_F32; ++k) v.w[k] = k < left ? v.w[k] : 0;
+#pragma unroll
+    for (int k = 0; k < 4 && DT == DT_F16; ++k)
+        v.w[k] = left >= 2 * k + 2 ? v.w[k] : left == 2 * k + 1 ? v.w[k] & 0xffffu : 0;
+    parts[0] = u4{v.w[0], v.w[1], v.w[2], v.w[3]};
+    if constexpr (DT == DT_F32) parts[1] = u4{v.w[4], v.w[5], v.w[6], v.w[7]};
+}
 
 template <int DT>
 __device__ __forceinline__ void finish_unit(Raw<DT>& v, int left, u4 (&parts)[DT == DT_F32 ? 3 : 1]) {
@@ -89,6 +101,159 @@ __device__ __forceinline__ void finish_unit(Raw<DT>& v, int left, u4 (&parts)[DT
 // v / d for 0 <= v < 2^16 by m = 2^32 / d rounded up (all ones: d = 1)
 __device__ __forceinline__ int quot(int v, uint32_t m) { return m == 0xffffffffu ? v : int(__umulhi(uint32_t(v), m)); }
 
+// Stage `units` units of 8 columns for T channels (zeros from `live` on): 8
+// lanes take 8 channels of a unit (conflict-free LDS writes), the next 8 the
+// next unit (whole lines of 8 planes).  Four loads in flight a lane (7 to 10,
+// with both tensors in one batch, measured 5 to 10 % slower).
+template <int DT, int WT, bool WHOLE>
+__device__ __forceinline__ void stage_units(const typename Elt<DT>::T* p, int64_t total, int n, int H, int W,
+                                            uint32_t h_m, int ch0, int chs, int row0, int grp0, int per,
+                                            uint32_t per_m, int live, int units, char* dst, int dst_plane) {
+    using E = typename Elt<DT>::T;
+    constexpr int NP = DT == DT_F32 ? 3 : 1, T = 32 * WT;
+    constexpr int NB = 4;
+    // image and row of padded row row0 (-1: the row before the first image)
+    const int im0 = row0 < 0 ? -1 : row0 / (H + 1), i0 = row0 - im0 * (H + 1), tid = threadIdx.x, plane = H * W;
+#pragma unroll
+    for (int h = 0; h < WT; ++h) {
+        const int ch = (tid & 7) + 8 * (tid >> 6) + 32 * h;
+        for (int u0 = (tid >> 3) & 7; u0 < units; u0 += 8 * NB) {
+            Raw<DT> raw[NB];
+            int left[NB];
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                const int u = u0 + 8 * k, r = quot(u, per_m), grp = grp0 + u - r * per;
+                const int d = quot(i0 + r, h_m), im = im0 + d, i = i0 + r - d * (H + 1) - 1;
+                const bool in = u < live && im >= 0 && i >= 0 && im < n && ch0 + ch < chs && grp >= 0 && 8 * grp < W;
+                left[k] = in ? W - 8 * grp : 0;
+                const int64_t at = in ? (int64_t(im) * chs + ch0 + ch) * plane + i * W + 8 * grp : 0;
+                if (at + 8 <= total) {
+                    __builtin_memcpy(raw[k].w, p + at, 8 * sizeof(E));
+                } else {                             // the end of the tensor
+                    E one[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) one[e] = at + e < total ? p[at + e] : E(0);
+                    __builtin_memcpy(raw[k].w, one, sizeof one);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                const int u = u0 + 8 * k;
+                if (u >= units) continue;
+                u4 parts[NP];
+                if constexpr (WHOLE) raw_unit<DT>(raw[k], left[k], parts);
+                else finish_unit<DT>(raw[k], left[k], parts);
+#pragma unroll
+                for (int s = 0; s < (WHOLE && NP > 1 ? 2 : NP); ++s)
+                    *reinterpret_cast<u4*>(dst + s * dst_plane + (u * T + ch) * 16) = parts[s];
+            }
+        }
+    }
+}
+
+// The sizes of a call, kept in LDS for sum_again: in registers they would take
+// scalars from the hot loop (1 to 1.5 % of its time).
+struct Sizes {
+    int64_t tiles;
+    int n, cin, H, W, cout, RT, GT, DU, U, gtiles, KS;
+    uint32_t gt_m, u_m, h_m;
+};
+
+// The sums of a block that the matrix cores cannot give: the tiles staged
+// again, whole, and summed by fp32 multiply-adds, 4 filters x 9 taps a lane (a
+// quarter of the filters a wave, or with WT = 2 the wave's own in four goes).
+// All that names a pixel is the same for the wave, so what lies outside the
+// image is skipped and not multiplied.  Measured, dv + db with one infinity in
+// the inputs, and in all of them (us; vector kernels, pixels read from memory
+// one by one, here): fp16 128 @ 28x28 b32 120, 1773, 126 and 120, 4055, 277; fp32
+// 256 @ 8x8 b256 255, 10245, 492 and 255, 12182, 558.
+template <int DT, int WT>
+__device__ __forceinline__ void sum_again(const typename Elt<DT>::T* x, const typename Elt<DT>::T* g, const Sizes& sz,
+                                          float* out, char* lds) {
+    constexpr int NP = DT == DT_F32 ? 3 : 1, T = 32 * WT;
+    auto u = [](int v) { return __builtin_amdgcn_readfirstlane(v); };    // the same in every lane
+    const int n = u(sz.n), cin = u(sz.cin), H = u(sz.H), W = u(sz.W), cout = u(sz.cout);
+    const int RT = u(sz.RT), GT = u(sz.GT), DU = u(sz.DU), U = u(sz.U), gtiles = u(sz.gtiles), KS = u(sz.KS);
+    const uint32_t gt_m = u(sz.gt_m), u_m = u(sz.u_m), h_m = u(sz.h_m);
+    const int f0 = blockIdx.x * T, c0 = blockIdx.y * T, ks = blockIdx.z;
+    const int64_t t0 = sz.tiles * ks / KS, t1 = sz.tiles * (ks + 1) / KS;
+    float* const dst = out + int64_t(ks) * cout * cin * 9;
+    const int uo = U > GT ? 1 : 0, last = RT * GT - 1, dy_plane = DU * T * 16, x_plane = (RT + 2) * U * T * 16;
+    char* const ldsG = lds;
+    char* const ldsX = lds + NP * dy_plane;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wf = WT == 2 ? (wave & 1) * 32 : 0, wc = WT == 2 ? (wave >> 1) * 32 : 0;
+    // the 8 columns of a unit
+    auto columns = [&](const char* unit, int plane_bytes, float* v) {
+        const u4 lo = *reinterpret_cast<const u4*>(unit);
+        if constexpr (DT == DT_F16) {
+            const h8 h = __builtin_bit_cast(h8, lo);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = float(h[e]);
+        } else {
+            const u4 hi = *reinterpret_cast<const u4*>(unit + plane_bytes);
+            __builtin_memcpy(v, &lo, 16);
+            __builtin_memcpy(v + 4, &hi, 16);
+        }
+    };
+    auto column = [&](const char* unit, int plane_bytes, int e) {
+        if constexpr (DT == DT_F16) return Elt<DT>::load(reinterpret_cast<const uint16_t*>(unit), e);
+        else return reinterpret_cast<const float*>(unit + (e >> 2) * plane_bytes)[e & 3];
+    };
+    const int w0 = WT == 2 ? 0 : wave;
+    const char* const xb = ldsX + (wc + (lane & 31)) * 16;
+#pragma unroll 1
+    for (int part = w0; part < (WT == 2 ? 4 : w0 + 1); ++part) {
+        const int fl = wf + 8 * part + 4 * (lane >> 5);
+        float sum[9][4] = {};
+        for (int64_t t = t0; t < t1; ++t) {
+            const int rt = int(t / gtiles), grp0 = int(t - int64_t(rt) * gtiles) * GT;
+            __syncthreads();
+            stage_units<DT, WT, true>(g, int64_t(n) * cout * H * W, n, H, W, h_m, f0, cout, rt * RT, grp0, GT,
+                                      gt_m, last + 1, DU, ldsG, dy_plane);
+            stage_units<DT, WT, true>(x, int64_t(n) * cin * H * W, n, H, W, h_m, c0, cin, rt * RT - 1, grp0 - uo, U,
+                                      u_m, (RT + 2) * U, (RT + 2) * U, ldsX, x_plane);
+            __syncthreads();
+#pragma unroll 1
+            for (int u = 0; u <= last; ++u) {
+                const int r = quot(u, gt_m), grp = u - r * GT, R = rt * RT + r;
+                const int im = R / (H + 1), i = R - im * (H + 1) - 1, j0 = 8 * (grp0 + grp);
+                if (im >= n || i < 0 || j0 >= W) continue;
+                const int cols = W - j0 < 8 ? W - j0 : 8;
+                const bool left = j0 > 0, right = j0 + 8 < W;
+                float gv[4][8];
+#pragma unroll
+                for (int f = 0; f < 4; ++f) columns(ldsG + (u * T + fl + f) * 16, dy_plane, gv[f]);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    if (i + q < 1 || i + q > H) continue;        // the row i + q - 1
+                    const char* const xu = xb + ((r + q) * U + grp + uo) * T * 16;
+                    float xv[10];                                // columns j0 - 1 ...
+                    columns(xu, x_plane, xv + 1);
+                    xv[0] = left ? column(xu - T * 16, x_plane, 7) : 0.f;
+                    xv[9] = right ? column(xu + T * 16, x_plane, 0) : 0.f;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        if (e >= cols) break;
+#pragma unroll
+                        for (int f = 0; f < 4; ++f) {
+                            if (e > 0 || left) sum[3 * q][f] = fmaf(gv[f][e], xv[e], sum[3 * q][f]);
+                            sum[3 * q + 1][f] = fmaf(gv[f][e], xv[e + 1], sum[3 * q + 1][f]);
+                            if (e + 1 < cols || right) sum[3 * q + 2][f] = fmaf(gv[f][e], xv[e + 2], sum[3 * q + 2][f]);
+                        }
+                    }
+                }
+            }
+        }
+        const int c = c0 + wc + (lane & 31);
+#pragma unroll
+        for (int f = 0; f < 4; ++f)
+#pragma unroll
+            for (int q = 0; q < 9; ++q)
+                if (c < cin && f0 + fl + f < cout) dst[(int64_t(f0 + fl + f) * 9 + q) * cin + c] = sum[q][f];
+    }
+}
+
 template <int DT, int WT>
 __global__ __launch_bounds__(256, 2) void k_wgrad_mfma(
     const typename Elt<DT>::T* __restrict__ x, const typename Elt<DT>::T* __restrict__ g, int n, int cin, int H,
@@ -96,6 +261,12 @@ __global__ __launch_bounds__(256, 2) void k_wgrad_mfma(
     constexpr int NP = DT == DT_F32 ? 3 : 1, T = 32 * WT;
     constexpr int NS = WT == 2 ? 2 : 8;                  // units in flight: one per half-wave of the same tile
     extern __shared__ __align__(16) char lds[];
+    __shared__ Sizes sizes;
+    if (threadIdx.x == 0) {
+        sizes.n = n, sizes.cin = cin, sizes.H = H, sizes.W = W, sizes.cout = cout;
+        sizes.RT = pl.RT, sizes.GT = pl.GT, sizes.DU = pl.DU, sizes.U = pl.U, sizes.gtiles = pl.gtiles, sizes.KS = pl.KS;
+        sizes.tiles = pl.tiles, sizes.gt_m = pl.gt_m, sizes.u_m = pl.u_m, sizes.h_m = pl.h_m;
+    }
     const int GT = pl.GT, U = pl.U, uo = U > GT ? 1 : 0;
     const int dy_plane = pl.DU * T * 16, x_plane = (pl.RT + 2) * U * T * 16;
     char* const ldsG = lds;
@@ -105,52 +276,6 @@ __global__ __launch_bounds__(256, 2) void k_wgrad_mfma(
     const int64_t t0 = pl.tiles * ks / pl.KS, t1 = pl.tiles * (ks + 1) / pl.KS;
     const int plane = H * W;
     const int64_t g_total = int64_t(n) * cout * plane, x_total = int64_t(n) * cin * plane;
-
-    // stage `units` units of 8 columns for T channels (zeros from `live` on):
-    // 8 lanes take 8 channels of a unit (conflict-free LDS writes), the next
-    // 8 the next unit (whole lines of 8 planes).  Four loads in flight a lane
-    // (7 to 10, with both tensors in one batch, measured 5 to 10 % slower)
-    using E = typename Elt<DT>::T;
-    auto stage = [&](const E* p, int64_t total, int ch0, int chs, int row0, int grp0, int per, uint32_t per_m,
-                     int live, int units, char* dst, int dst_plane) {
-        constexpr int NB = 4;
-        // image and row of padded row row0 (-1: the row before the first image)
-        const int im0 = row0 < 0 ? -1 : row0 / (H + 1), i0 = row0 - im0 * (H + 1);
-#pragma unroll
-        for (int h = 0; h < WT; ++h) {
-            const int ch = (tid & 7) + 8 * (tid >> 6) + 32 * h;
-            for (int u0 = (tid >> 3) & 7; u0 < units; u0 += 8 * NB) {
-                Raw<DT> raw[NB];
-                int left[NB];
-#pragma unroll
-                for (int k = 0; k < NB; ++k) {
-                    const int u = u0 + 8 * k, r = quot(u, per_m), grp = grp0 + u - r * per;
-                    const int d = quot(i0 + r, pl.h_m), im = im0 + d, i = i0 + r - d * (H + 1) - 1;
-                    const bool in = u < live && im >= 0 && i >= 0 && im < n && ch0 + ch < chs && grp >= 0 && 8 * grp < W;
-                    left[k] = in ? W - 8 * grp : 0;
-                    const int64_t at = in ? (int64_t(im) * chs + ch0 + ch) * plane + i * W + 8 * grp : 0;
-                    if (at + 8 <= total) {
-                        __builtin_memcpy(raw[k].w, p + at, 8 * sizeof(E));
-                    } else {                             // the end of the tensor
-                        E one[8];
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) one[e] = at + e < total ? p[at + e] : E(0);
-                        __builtin_memcpy(raw[k].w, one, sizeof one);
-                    }
-                }
-#pragma unroll
-                for (int k = 0; k < NB; ++k) {
-                    const int u = u0 + 8 * k;
-                    if (u >= units) continue;
-                    u4 parts[NP];
-                    finish_unit<DT>(raw[k], left[k], parts);
-#pragma unroll
-                    for (int s = 0; s < NP; ++s)
-                        *reinterpret_cast<u4*>(dst + s * dst_plane + (u * T + ch) * 16) = parts[s];
-                }
-            }
-        }
-    };
 
     // this half-wave's filters, channels and units
     const int wf = WT == 2 ? (wave & 1) * 32 : 0, wc = WT == 2 ? (wave >> 1) * 32 : 0;
@@ -171,8 +296,10 @@ __global__ __launch_bounds__(256, 2) void k_wgrad_mfma(
     for (int64_t t = t0; t < t1; ++t) {
         const int rt = int(t / pl.gtiles), grp0 = int(t - int64_t(rt) * pl.gtiles) * GT, row0 = rt * pl.RT;
         if (t > t0) __syncthreads();
-        stage(g, g_total, f0, cout, row0, grp0, GT, pl.gt_m, last + 1, pl.DU, ldsG, dy_plane);
-        stage(x, x_total, c0, cin, row0 - 1, grp0 - uo, U, pl.u_m, (pl.RT + 2) * U, (pl.RT + 2) * U, ldsX, x_plane);
+        stage_units<DT, WT, false>(g, g_total, n, H, W, pl.h_m, f0, cout, row0, grp0, GT, pl.gt_m, last + 1, pl.DU, ldsG,
+                                   dy_plane);
+        stage_units<DT, WT, false>(x, x_total, n, H, W, pl.h_m, c0, cin, row0 - 1, grp0 - uo, U, pl.u_m,
+                                   (pl.RT + 2) * U, (pl.RT + 2) * U, ldsX, x_plane);
         __syncthreads();
         for (int k0 = 0; k0 < steps; k0 += CH) {
             sign = -sign;
@@ -279,40 +406,21 @@ __global__ __launch_bounds__(256, 2) void k_wgrad_mfma(
                 again |= u >= 0xff000000u || (DT == DT_F32 && u - 1 < 2u * 0x12800000u - 1);
             }
     float* const dst = out + int64_t(ks) * cout * cin * 9;
-    if (__syncthreads_or(int(again))) {
-        const int rows = n * (H + 1);
-        for (int e = tid; e < T * T * 9; e += 256) {
-            const int q = e % 9, c = c0 + (e / 9) % T, f = f0 + e / (9 * T);
-            if (c >= cin || f >= cout) continue;
-            float s = 0.f;
-            for (int64_t t = t0; t < t1; ++t) {
-                const int rt = int(t / pl.gtiles), grp0 = int(t - int64_t(rt) * pl.gtiles) * GT;
-                for (int R = rt * pl.RT; R < (rt + 1) * pl.RT && R < rows; ++R) {
-                    const int im = R / (H + 1), i = R - im * (H + 1) - 1, ir = i + q / 3 - 1;
-                    if (i < 0 || ir < 0 || ir >= H) continue;
-                    const typename Elt<DT>::T* const gp = g + (int64_t(im) * cout + f) * plane + i * W;
-                    const typename Elt<DT>::T* const xp = x + (int64_t(im) * cin + c) * plane + ir * W;
-                    for (int j = 8 * grp0; j < 8 * (grp0 + GT) && j < W; ++j) {
-                        const int jr = j + q % 3 - 1;
-                        if (jr >= 0 && jr < W) s = fmaf(Elt<DT>::load(gp, j), Elt<DT>::load(xp, jr), s);
-                    }
-                }
-            }
-            dst[(int64_t(f) * 9 + q) * cin + c] = s;
-        }
-        return;
-    }
     // D[i][j] of tap q: filter f0 + wf + i, channel c0 + wc + j
     const int c = c0 + wc + (lane & 31);
-    if (c >= cin) return;
+    if (c < cin) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int f = f0 + wf + 8 * (r / 4) + 4 * (lane >> 5) + r % 4;
-        if (f >= cout) continue;
+        for (int r = 0; r < 16; ++r) {
+            const int f = f0 + wf + 8 * (r / 4) + 4 * (lane >> 5) + r % 4;
+            if (f >= cout) continue;
 #pragma unroll
-        for (int q = 0; q < 9; ++q)
-            if (owns(q, r)) dst[(int64_t(f) * 9 + q) * cin + c] = acc[q][r];
+            for (int q = 0; q < 9; ++q)
+                if (owns(q, r)) dst[(int64_t(f) * 9 + q) * cin + c] = acc[q][r];
+        }
     }
+    // over what was just written, so that the sums need no registers any more
+    if (__syncthreads_or(int(again)))
+        sum_again<DT, WT>(x, g, sizes, out, lds);
 }
 
 // dw[f][c][q] = the sum of the KS slots part[s][f][q][c] in a fixed order:
