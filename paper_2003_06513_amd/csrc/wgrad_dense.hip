@@ -406,6 +406,8 @@ __global__ __launch_bounds__(256, 2) void k_wgrad_mfma(
                 again |= u >= 0xff000000u || (DT == DT_F32 && u - 1 < 2u * 0x12800000u - 1);
             }
     float* const dst = out + int64_t(ks) * cout * cin * 9;
+    // asked before the store: a barrier after it would wait for it
+    const int redo = __builtin_amdgcn_readfirstlane(__syncthreads_or(int(again)));
     // D[i][j] of tap q: filter f0 + wf + i, channel c0 + wc + j
     const int c = c0 + wc + (lane & 31);
     if (c < cin) {
@@ -419,7 +421,7 @@ __global__ __launch_bounds__(256, 2) void k_wgrad_mfma(
         }
     }
     // over what was just written, so that the sums need no registers any more
-    if (__syncthreads_or(int(again)))
+    if (redo)
         sum_again<DT, WT>(x, g, sizes, out, lds);
 }
 
