@@ -31,8 +31,14 @@
 //
 // Infinities and NaNs: the dense tile multiplies pruned weights (zero) by
 // every staged input, which must not turn a non-finite input that no kept
-// weight reads into NaN.  A block that staged a non-finite value computes its
-// outputs again with the sum over the kept weights alone.
+// weight reads into NaN.  A block that staged one goes over its channels four
+// times more, by the matrix cores again: for the sums, with 1 or -1 in its
+// place; for the number of terms that are infinite or NaN; and twice for the
+// signs of the infinite ones, from which the outputs that read one follow.  A
+// kept weight that is zero is -0 in the tile, a pruned one 0.  Measured with one
+// infinity in the input, and with all of it infinite (us a call; vector
+// kernels, kept weights from memory one by one, here): 128 @ 28x28 b32 47, 1256,
+// 100 and 47, 1445, 110; 512 @ 28x28 b64 882, 10867, 521 and 882, 62963, 2175.
 //
 // Layout of v_mfma_f32_32x32x16_f16: lane l supplies A[l % 32][8 (l / 32) + j]
 // and B[8 (l / 32) + j][l % 32], j = 0..7; register r of the result holds
@@ -52,7 +58,8 @@ typedef uint32_t u2 __attribute__((ext_vector_type(2)));
 
 // The weight tiles of a call, decoded from the compressed storage:
 //   wt[f / 64][c / 32][tap][(c / 8) % 4][f % 64][c % 8],
-// zero where pruned and past cin and cout; f counts reordered filters.  A
+// zero where pruned and past cin and cout, a kept zero as -0; f counts
+// reordered filters.  A
 // block owns 8 filters x 128 channels: each of its waves scans a filter's
 // kernels, scatters the weights to LDS, and all write 16-byte units.
 constexpr int kDF = 8, kDC = 128;
@@ -87,10 +94,11 @@ __global__ __launch_bounds__(512) void k_weight_tiles(const int32_t* __restrict_
                 if (kb + 64 * j + lane >= k1 || uint32_t(c[j]) >= uint32_t(kDC) || c0 + c[j] >= g.cin || p[j] >= g.m)
                     continue;
                 const uint32_t tp = g.taps[p[j]];
-                t[fl][(tp & 15) * kDC + c[j]] = uint16_t(v[j][0]);
-                t[fl][((tp >> 4) & 15) * kDC + c[j]] = uint16_t(v[j][0] >> 16);
-                t[fl][((tp >> 8) & 15) * kDC + c[j]] = uint16_t(v[j][1]);
-                t[fl][(tp >> 12) * kDC + c[j]] = uint16_t(v[j][1] >> 16);
+                auto kept = [](uint32_t h) { return uint16_t(h & 0x7fffu ? h : 0x8000u); };
+                t[fl][(tp & 15) * kDC + c[j]] = kept(v[j][0]);
+                t[fl][((tp >> 4) & 15) * kDC + c[j]] = kept(v[j][0] >> 16);
+                t[fl][((tp >> 8) & 15) * kDC + c[j]] = kept(v[j][1]);
+                t[fl][(tp >> 12) * kDC + c[j]] = kept(v[j][1] >> 16);
             }
         }
     }
@@ -106,11 +114,36 @@ __global__ __launch_bounds__(512) void k_weight_tiles(const int32_t* __restrict_
     }
 }
 
+// Two fp16 values: all ones in each half whose bit 15 is set in t.
+__device__ __forceinline__ uint32_t halves(uint32_t t) { return ((t & 0x80008000u) >> 15) * 0xffffu; }
+__device__ __forceinline__ uint32_t not_finite(uint32_t w) { return halves((w & 0x7c007c00u) + 0x04000400u); }
+__device__ __forceinline__ uint32_t signed_one(uint32_t w) { return (w & 0x80008000u) | 0x3c003c00u; }
+
+// Inputs and weights as the sweeps multiply them.  0: the sums, a non-finite
+// input as 1 or -1.  1: 1 for each non-finite input and kept weight (the number
+// of such terms); 2: the sign of each infinite input and of each weight; 3:
+// the same, times -2.  After 1 and 2 a sum is twice the +infinities plus the
+// NaNs, after 3 twice the -infinities plus the NaNs.
+__device__ __forceinline__ uint32_t sweep_x(uint32_t w, int sweep) {
+    const uint32_t m = not_finite(w);
+    if (sweep == 0) return (w & ~m) | (m & signed_one(w));
+    if (sweep == 1) return m & 0x3c003c00u;
+    const uint32_t inf = m & ~halves(((w & 0x03ff03ffu) + 0x03ff03ffu) << 5);
+    return inf & (sweep == 2 ? signed_one(w) : signed_one(~w) + 0x04000400u);
+}
+__device__ __forceinline__ uint32_t sweep_w(uint32_t w, int sweep) {
+    const uint32_t mag = w & 0x7fff7fffu, nonzero = mag + 0x7fff7fffu;
+    if (sweep == 0) return w;
+    if (sweep == 1) return halves(nonzero | w) & 0x3c003c00u;
+    return halves(nonzero) & ~halves(mag + 0x03ff03ffu) & signed_one(w);
+}
+
 template <int NT, int G, bool ALIGNED, int MI>
-__global__ __launch_bounds__(256 * G, 2) void k_conv_mfma(
-    const uint16_t* __restrict__ x, const uint16_t* __restrict__ wtiles, const int32_t* __restrict__ perm,
-    const int32_t* __restrict__ fptr, const int32_t* __restrict__ cin_idx, const uint8_t* __restrict__ pat_id,
-    const uint16_t* __restrict__ values, const uint16_t* __restrict__ bias, MGeo g, uint16_t* __restrict__ y) {
+__global__ __launch_bounds__(256 * G, 2) void k_conv_mfma(const uint16_t* __restrict__ x,
+                                                          const uint16_t* __restrict__ wtiles,
+                                                          const int32_t* __restrict__ perm,
+                                                          const uint16_t* __restrict__ bias, MGeo g,
+                                                          uint16_t* __restrict__ y) {
     constexpr int kThreads = 256 * G, KC = kKC * G, KQ = KC / 8;
     // four waves each take 32 channels of a stage: 256 pixels: 4 of 64 filters x 64 pixels; 128: 2 x 2 of 32 x 64;
     // 64: 2 x 2 of 32 x 32
@@ -164,7 +197,10 @@ __global__ __launch_bounds__(256 * G, 2) void k_conv_mfma(
     }
 
     // zero the X tile once: padding rows and columns are never written
-    for (int e = tid; e < KQ * g.Lst; e += kThreads) *reinterpret_cast<u4*>(ldsX + e * 16) = u4{0, 0, 0, 0};
+    auto zero_x = [&]() {
+        for (int e = tid; e < KQ * g.Lst; e += kThreads) *reinterpret_cast<u4*>(ldsX + e * 16) = u4{0, 0, 0, 0};
+    };
+    zero_x();
     if (tid < kF) {
         const int p = f0 + tid < g.cout ? perm[f0 + tid] : -1;
         perm_s[tid] = p;
@@ -211,64 +247,65 @@ __global__ __launch_bounds__(256 * G, 2) void k_conv_mfma(
     u2 xv[MI][8];
     uint32_t hv[8];
     uint32_t bad = 0;
-    auto fetch = [&](int c0) {
-        // channels past cin read what follows (their weights are zero) or,
-        // past x, zero
-        const uint32_t so = uint32_t(c0 * plane) * 2u, cs = uint32_t(plane) * 2u;
+    const uint32_t cs = uint32_t(plane) * 2u;
+    // channels past cin read what follows (their weights are zero) or, past
+    // x, zero
+    auto load = [&](uint32_t at, uint32_t so, u2 (&v)[8]) {
 #pragma unroll
-        for (int s = 0; s < MI; ++s) {
-            if (kThreads * s >= items) continue;         // the same for the whole block
-#pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                const uint32_t vo = goff[s] + (so + uint32_t(c) * cs);
-                if constexpr (ALIGNED) {
-                    xv[s][c] = __builtin_amdgcn_raw_buffer_load_b64(xr, int(vo), 0, 0);
-                } else {
-                    xv[s][c] = u2{0, 0};
-                    if (vo + 8u <= uint32_t(g.x_bytes))
-                        __builtin_memcpy(&xv[s][c], reinterpret_cast<const char*>(x) + vo, 8);
-                }
+        for (int c = 0; c < 8; ++c) {
+            const uint32_t vo = at + (so + uint32_t(c) * cs);
+            if constexpr (ALIGNED) {
+                v[c] = __builtin_amdgcn_raw_buffer_load_b64(xr, int(vo), 0, 0);
+            } else {
+                v[c] = u2{0, 0};
+                if (vo + 8u <= uint32_t(g.x_bytes))
+                    __builtin_memcpy(&v[c], reinterpret_cast<const char*>(x) + vo, 8);
             }
-        }
-        if (halo) {
-#pragma unroll
-            for (int c = 0; c < 8; ++c)
-                hv[c] = __builtin_amdgcn_raw_buffer_load_b16(xr, int(hgoff + (so + uint32_t(c) * cs)), 0, 0);
         }
     };
+    auto load_halo = [&](uint32_t at, uint32_t so, uint32_t (&v)[8]) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) v[c] = __builtin_amdgcn_raw_buffer_load_b16(xr, int(at + (so + uint32_t(c) * cs)), 0, 0);
+    };
+    auto fetch = [&](int c0) {
+#pragma unroll
+        for (int s = 0; s < MI; ++s)
+            if (kThreads * s < items) load(goff[s], uint32_t(c0) * cs, xv[s]);       // the same for the whole block
+        if (halo) load_halo(hgoff, uint32_t(c0) * cs, hv);
+    };
     // exponent all ones in either half sets bit 15 or 31
-    auto test = [&](uint32_t w) { bad |= (w & 0x7c007c00u) + 0x04000400u; };
-    auto stage_x = [&]() {
+    auto test = [&](uint32_t w) {
+        bad |= (w & 0x7c007c00u) + 0x04000400u;
+        return w;
+    };
+    // 4 columns x 8 channels, and a halo column's 8, to LDS through `as`
+    auto put = [&](int at, const u2 (&v)[8], auto as) {
+        uint32_t w[2][8];
 #pragma unroll
-        for (int s = 0; s < MI; ++s) {
-            if (loff[s] < 0) continue;
-            uint32_t w[2][8];
-#pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                w[0][c] = xv[s][c].x;
-                w[1][c] = xv[s][c].y;
-                test(w[0][c]);
-                test(w[1][c]);
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                u4 o;
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    o[c] = __builtin_amdgcn_perm(w[e / 2][2 * c + 1], w[e / 2][2 * c],
-                                                 e & 1 ? 0x07060302u : 0x05040100u);
-                *reinterpret_cast<u4*>(ldsX + loff[s] + e * 16) = o;
-            }
+        for (int c = 0; c < 8; ++c) {
+            w[0][c] = as(v[c].x);
+            w[1][c] = as(v[c].y);
         }
-        if (halo && hloff >= 0) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
             u4 o;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                o[c] = __builtin_amdgcn_perm(hv[2 * c + 1], hv[2 * c], 0x05040100u);
-                test(o[c]);
-            }
-            *reinterpret_cast<u4*>(ldsX + hloff) = o;
+            for (int c = 0; c < 4; ++c)
+                o[c] = __builtin_amdgcn_perm(w[e / 2][2 * c + 1], w[e / 2][2 * c], e & 1 ? 0x07060302u : 0x05040100u);
+            *reinterpret_cast<u4*>(ldsX + at + e * 16) = o;
         }
+    };
+    auto put_halo = [&](int at, const uint32_t (&v)[8], auto as) {
+        u4 o;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) o[c] = as(__builtin_amdgcn_perm(v[2 * c + 1], v[2 * c], 0x05040100u));
+        *reinterpret_cast<u4*>(ldsX + at) = o;
+    };
+    auto stage_x = [&]() {
+#pragma unroll
+        for (int s = 0; s < MI; ++s)
+            if (loff[s] >= 0) put(loff[s], xv[s], test);
+        if (halo && hloff >= 0) put_halo(hloff, hv, test);
     };
 
     // the stage's weight tile: 36 KiB in the LDS order, 9 x 16 bytes a thread
@@ -333,70 +370,148 @@ __global__ __launch_bounds__(256 * G, 2) void k_conv_mfma(
         __syncthreads();
     }
 
-    // one staged value of the block not finite: sum the kept weights alone
-    if (__syncthreads_or(int(bad & 0x80008000u))) {
-        for (int e = tid; e < kF * NT; e += kThreads) {
-            const int f = e / NT, o = o0 + e % NT;
-            if (f0 + f >= g.cout || o >= g.slots) continue;
-            prow(o, img, i, j);
-            if (j0 + j >= g.OW) continue;
-            float s = 0.f;
-            const int k1 = fptr[f0 + f + 1] < g.keep ? fptr[f0 + f + 1] : g.keep;
-            for (int k = fptr[f0 + f] > 0 ? fptr[f0 + f] : 0; k < k1; ++k) {
-                const int c = cin_idx[k], p = pat_id[k];
-                if (uint32_t(c) >= uint32_t(g.cin) || p >= g.m) continue;
-                const uint32_t tp4 = g.taps[p];
-                const uint16_t* xp = x + (int64_t(img) * g.cin + c) * plane;
-                for (int t = 0; t < 4; ++t) {
-                    const int q = (tp4 >> (4 * t)) & 15;
-                    const int ih = g.S * i + q / 3 - 1, iw = g.S * (j0 + j) + q % 3 - 1;
-                    if (ih >= 0 && ih < g.H && iw >= 0 && iw < g.W)
-                        s = fmaf(Elt<DT_F16>::load(values, 4 * int64_t(k) + t), Elt<DT_F16>::load(xp, ih * g.W + iw), s);
-                }
-            }
-            s += bias_s[f];
-            if (g.relu) s = s > 0.f ? s : 0.f;
-            y[(int64_t(img) * g.cout + perm_s[f]) * g.OH * g.OW + i * g.OW + j0 + j] = Elt<DT_F16>::from_f(s);
-        }
-        return;
-    }
-
     // the second group's sums go to the first through LDS
-    if constexpr (G == 2) {
-        float* const red = reinterpret_cast<float*>(lds) + wave * (FI * NI * 1024) + lane;
+    auto meet = [&]() {
+        if constexpr (G == 2) {
+            float* const red = reinterpret_cast<float*>(lds) + wave * (FI * NI * 1024) + lane;
+#pragma unroll
+            for (int a = 0; a < FI; ++a)
+#pragma unroll
+                for (int t = 0; t < NI; ++t)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        if (grp) red[((a * NI + t) * 16 + r) * 64] = acc[a][t][r];
+            __syncthreads();
+#pragma unroll
+            for (int a = 0; a < FI; ++a)
+#pragma unroll
+                for (int t = 0; t < NI; ++t)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        if (!grp) acc[a][t][r] += red[((a * NI + t) * 16 + r) * 64];
+        }
+    };
+    // each output of this lane: its number, filter, place
+    const int oplane = g.OH * g.OW;
+    auto outputs = [&](int lane, auto put) {
+#pragma unroll
+        for (int a = 0; a < FI; ++a)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int f = wf + 32 * a + 8 * (r / 4) + 4 * (lane >> 5) + r % 4;
+                if (f0 + f >= g.cout) continue;
+                uint16_t* const yf = y + int64_t(perm_s[f]) * oplane;
+                const float bv = bias_s[f];
+#pragma unroll
+                for (int t = 0; t < NI; ++t)
+                    if (live[t]) put(a, t, r, bv, yf + ybase[t]);
+            }
+    };
+    auto store = [&](int lane) {
+        if (grp == 0)
+            outputs(lane, [&](int a, int t, int r, float bv, uint16_t* to) {
+                float v = acc[a][t][r] + bv;
+                if (g.relu) v = v > 0.f ? v : 0.f;
+                *to = Elt<DT_F16>::from_f(v);
+            });
+    };
+    // asked before the store: a barrier after it would wait for it
+    const int again = __builtin_amdgcn_readfirstlane(__syncthreads_or(int(bad & 0x80008000u)));
+    meet();
+    store(lane);
+    if (!again) return;
+
+    // the lane once more, so that nothing of the first store is kept for the
+    // next (the registers are the hot loop's)
+    auto again_lane = [&]() {
+        int l = lane;
+        asm volatile("" : "+v"(l));
+        return l;
+    };
+    // the outputs of this lane whose sum is infinite above and below (NaN:
+    // both), a bit each; by integers, so that no lane masks pile up
+    constexpr int MW = (FI * NI + 1) / 2;
+    uint32_t pos[MW] = {}, neg[MW] = {};
+    auto mark = [&](auto add) {
 #pragma unroll
         for (int a = 0; a < FI; ++a)
 #pragma unroll
             for (int t = 0; t < NI; ++t)
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    if (grp) red[((a * NI + t) * 16 + r) * 64] = acc[a][t][r];
+                for (int r = 0; r < 16; ++r) {
+                    const float v = acc[a][t][r];
+                    add(__builtin_bit_cast(uint32_t, v), (a * NI + t) / 2, ((a * NI + t) % 2) * 16 + r);
+                }
+    };
+#pragma unroll 1
+    for (int sweep = 0; sweep < 4; ++sweep) {
+        if (sweep < 2) {
+#pragma unroll
+            for (int a = 0; a < FI; ++a)
+#pragma unroll
+                for (int t = 0; t < NI; ++t)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[a][t][r] = 0.f;
+        }
+        __syncthreads();
+        zero_x();                                        // meet() may have used its place
+#pragma unroll 1
+        for (int c0 = 0; c0 < g.cin; c0 += KC) {
+            __syncthreads();
+            auto as = [&](uint32_t w) { return sweep_x(w, sweep); };
+#pragma unroll
+            for (int s = 0; s < MI; ++s) {
+                u2 v[8];
+                if (kThreads * s < items) load(goff[s], uint32_t(c0) * cs, v);
+                if (loff[s] >= 0) put(loff[s], v, as);
+            }
+            if (halo) {
+                uint32_t v[8];
+                load_halo(hgoff, uint32_t(c0) * cs, v);
+                if (hloff >= 0) put_halo(hloff, v, as);
+            }
+#pragma unroll
+            for (int e = 0; e < AJ; ++e) {
+                u4 v = wt[int64_t(c0 / KC) * (AJ * kThreads) + e * kThreads];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) v[k] = sweep_w(v[k], sweep);
+                *reinterpret_cast<u4*>(ldsA + (tid + e * kThreads) * 16) = v;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int ks = 0; ks < kKC / 16; ++ks) mfma(ks);
+        }
+        if (sweep == 0) {
+            __syncthreads();
+            meet();
+            mark([&](uint32_t u, int i, int k) {
+                const uint32_t mag = u & 0x7fffffffu, inf = (mag + 0x00800000u) >> 31, nan = (mag + 0x007fffffu) >> 31;
+                pos[i] |= (inf & (nan | ~(u >> 31))) << k;
+                neg[i] |= (inf & (nan | (u >> 31))) << k;
+            });
+            store(again_lane());
+        } else if (sweep == 2) {                         // whole numbers, none negative
+            mark([&](uint32_t u, int i, int k) { pos[i] |= (u < 1u ? u : 1u) << k; });
+        } else if (sweep == 3) {
+            mark([&](uint32_t u, int i, int k) { neg[i] |= (u < 1u ? u : 1u) << k; });
+        }
+    }
+    if constexpr (G == 2) {                              // each group has seen half of the channels
+        uint32_t* const red = reinterpret_cast<uint32_t*>(lds) + (tid & 255);
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < MW; ++i)
+            if (grp) red[512 * i] = pos[i], red[512 * i + 256] = neg[i];
         __syncthreads();
         if (grp) return;
 #pragma unroll
-        for (int a = 0; a < FI; ++a)
-#pragma unroll
-            for (int t = 0; t < NI; ++t)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[a][t][r] += red[((a * NI + t) * 16 + r) * 64];
+        for (int i = 0; i < MW; ++i) pos[i] |= red[512 * i], neg[i] |= red[512 * i + 256];
     }
-    const int oplane = g.OH * g.OW;
-#pragma unroll
-    for (int a = 0; a < FI; ++a)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int f = wf + 32 * a + 8 * (r / 4) + 4 * (lane >> 5) + r % 4;
-            if (f0 + f >= g.cout) continue;
-            const float bv = bias_s[f];
-            uint16_t* const yf = y + int64_t(perm_s[f]) * oplane;
-#pragma unroll
-            for (int t = 0; t < NI; ++t)
-                if (live[t]) {
-                    float v = acc[a][t][r] + bv;
-                    if (g.relu) v = v > 0.f ? v : 0.f;
-                    yf[ybase[t]] = Elt<DT_F16>::from_f(v);
-                }
-        }
+    outputs(again_lane(), [&](int a, int t, int r, float, uint16_t* to) {
+        const int i = (a * NI + t) / 2, k = ((a * NI + t) % 2) * 16 + r;
+        const bool p = (pos[i] >> k) & 1, n = (neg[i] >> k) & 1;
+        if (p || n) *to = g.relu ? (p && !n ? 0x7c00 : 0) : n ? (p ? 0x7e00 : 0xfc00) : 0x7c00;
+    });
 }
 
 // A tile of NT pixels and G groups of waves; false when the kernel does not
@@ -447,7 +562,6 @@ hipError_t launch(const MPlan& p, const PackedView& pk, const ConvArgs& a, hipSt
     const int grid = (p.g.nblocks + 7) / 8 * 8;
     hipLaunchKernelGGL((k_conv_mfma<NT, G, ALIGNED, MI>), dim3(unsigned(grid)), dim3(256 * G), unsigned(p.lds), s,
                        static_cast<const uint16_t*>(a.x), static_cast<const uint16_t*>(a.ws), pk.filter_perm,
-                       pk.filter_ptr, pk.cin_idx, pk.pat_id, static_cast<const uint16_t*>(pk.values),
                        static_cast<const uint16_t*>(a.bias), p.g, static_cast<uint16_t*>(a.y));
     return hipGetLastError();
 }

@@ -107,3 +107,35 @@ def test_non_finite_and_subnormal_inputs(case):
     B.conv3x3_fwd_strided(prep.layer, prep.packed, xs, z, stride, algo=1)
     torch.cuda.synchronize()
     assert torch.equal(y, z) and float(z.abs().max()) > 0
+
+
+@pytest.mark.parametrize("relu", [False, True])
+@pytest.mark.parametrize("case", CASES, ids=["x".join(map(str, c)) for c in CASES])
+def test_non_finite_classes(case, relu):
+    """Every tile, with kept weights that are zero of either sign (0 * inf is
+    NaN, a pruned weight's is nothing), few and many infinities of both signs
+    in reach of one output, NaNs, and a bias: the class of every output is that
+    of the one-output-per-lane kernel, and the finite ones agree."""
+    torch = torch_mod()
+    n, cin, cout, h, w, drop, stride, m = case
+    prep, packed, masks, x = _make(case)
+    g = np.random.default_rng(11)
+    v = prep.packed.values
+    v[torch.from_numpy(g.random(v.numel()) < 0.1).cuda()] = 0.0
+    v[torch.from_numpy(g.random(v.numel()) < 0.1).cuda()] = -0.0
+    k = max(1, x.size // 100000)
+    for val in (np.inf, -np.inf, np.nan):
+        x.reshape(-1)[g.integers(0, x.size, k)] = val
+    x[n - 1, :2, h - 1, 1], x[0, :2, 0, 0] = np.inf, -np.inf
+    x[n // 2, :, h // 2] = np.inf                   # a whole row of every channel
+    xd, bd = dev(x), dev(inputs.bias_vector(9, cout, np.float16))
+    y = torch.empty((n, cout, (h - 1) // stride + 1, (w - 1) // stride + 1), dtype=torch.float16, device="cuda")
+    z = torch.empty_like(y)
+    note("mfma classes %s relu %d" % (case, relu))
+    B.conv3x3_fwd_strided(prep.layer, prep.packed, xd, y, stride, bias=bd, relu=relu)
+    B.conv3x3_fwd_strided(prep.layer, prep.packed, xd, z, stride, bias=bd, relu=relu, algo=1)
+    torch.cuda.synchronize()
+    assert torch.equal(torch.isnan(y), torch.isnan(z))
+    assert torch.equal(torch.where(torch.isinf(y), y, 0), torch.where(torch.isinf(z), z, 0))
+    ok = torch.isfinite(z)
+    assert bool(ok.any()) and float((y[ok].float() - z[ok].float()).abs().max()) <= 2 * 2.0 ** -11 * float(z[ok].float().abs().max())
