@@ -214,7 +214,11 @@ psc_status psc_conv3x3_fwd_strided(const psc_layer *layer, const psc_packed *pac
  * 256-byte aligned (NULL: exactly those calls).  With it algo 0 may run
  * layers on the matrix cores: each call then decodes the packed weights into
  * the buffer and multiplies the dense tiles, fp16 values as they are and fp32
- * values in three bf16 parts whose sum is exact, with fp32 sums.  The buffer
+ * values in three bf16 parts, with fp32 sums.  The parts of a magnitude of 2^-110
+ * or more add up to it, of a smaller one to within 2^-134; sums for which that
+ * could matter, as well as those that are not finite, are taken again by fp32
+ * multiply-adds, so that they keep the error bound of those (give or take
+ * 2^-115 per product).  The buffer
  * holds nothing from one call to the next.  Calls on the same *packed, its
  * arrays unchanged, may share one buffer, also on several streams (each writes
  * the same bytes); any other calls that may overlap need one each. */
@@ -370,8 +374,8 @@ psc_status psc_dense3x3_fwd(int32_t dtype, const void *d_x, int32_t n, int32_t c
 /* The same with a scratch buffer of the caller's, at least
  * psc_dense3x3_fwd_workspace bytes and 256-byte aligned (NULL: exactly that
  * call).  With it fp32 layers of at least 16 input channels and 32 filters run
- * on the 16-bit matrix cores, each value in three bf16 parts whose sum is exact.
- * The buffer holds nothing from one call to the next; calls that may overlap
+ * on the 16-bit matrix cores, each value in three bf16 parts (as in
+ * psc_conv3x3_fwd_ws).  The buffer holds nothing from one call to the next; calls that may overlap
  * need one each. */
 psc_status psc_dense3x3_fwd_workspace(int32_t dtype, int32_t cin, int32_t cout, size_t *bytes);
 psc_status psc_dense3x3_fwd_ws(int32_t dtype, const void *d_x, int32_t n, int32_t cin,

@@ -18,9 +18,14 @@
 // 16 channels.  LDS reads bound it: 9 KB for the 12 MFMAs of a wave and tap
 // (NT = 256), 94 B a clock and CU of the 128 that there are.
 //
-// A block with a sum that is not finite, or nonzero below 2^-90 (where bf16
-// parts run out of range), computes its outputs again with fp32 multiply-adds
-// of the kept weights.
+// Range.  Parts are whole down to 2^-133 (subnormals are kept): a value of 2^-110
+// or more is exactly the sum of its parts, a smaller one within 2^-134.  With the
+// other factors below 2^19, n products are so within n 2^-115 of those of fp32,
+// 2^-25 n of a sum of 2^-90.  A block computes its outputs again with fp32
+// multiply-adds of the kept weights if a sum is not finite, or nonzero below
+// 2^-90, or if inputs below 2^-110 meet weights of 2^19 or more or the other way
+// round: k_split_* write what the weights are, and the inputs are looked at only
+// where it matters (weights outside 2^-110 .. 2^19).
 //
 // Measured (us a call, fp32 MFMA first): dense 64 @ 32x32 b32 42 -> 22,
 // 128 @ 28x28 b32 128 -> 64, 256 @ 14x14 b32 147 -> 60; error against 64 bits
@@ -60,6 +65,33 @@ __device__ __forceinline__ void split8(const float (&v)[8], u4 (&o)[3]) {
     for (int s = 0; s < 3; ++s) o[s] = u4{w[s][0], w[s][1], w[s][2], w[s][3]};
 }
 
+// The smallest nonzero and the largest magnitude of some values, as twice their
+// bits (less one, so that zero is the largest).
+struct Range {
+    uint32_t lo = ~0u, hi = 0;
+    __device__ __forceinline__ void add(float v) {
+        const uint32_t u = __builtin_bit_cast(uint32_t, v) << 1;
+        lo = u - 1 < lo ? u - 1 : lo;
+        hi = u > hi ? u : hi;
+    }
+    // some below 2^-110: 1; some of 2^19 or more: 2
+    __device__ __forceinline__ uint32_t bits() const {
+        return (lo < 2u * 0x08800000u - 1 ? 1u : 0u) | (hi >= 2u * 0x49000000u ? 2u : 0u);
+    }
+};
+
+// The range of a wave's weights to its word of `flags`; at most kFlags words for
+// each 64 filters x 16 channels.  Waves write and read by themselves: a
+// reduction over the block took 4 us of 90 (64->128 @ 32x32, stride 2, b256).
+constexpr int kFlags = 64;
+__device__ __forceinline__ uint32_t wave_or(uint32_t bits) {
+    return (__ballot(bits & 1) ? 1u : 0u) | (__ballot(bits & 2) ? 2u : 0u);
+}
+__device__ __forceinline__ void put_range(const Range& range, uint32_t* block) {
+    const uint32_t r = wave_or(range.bits());
+    if ((threadIdx.x & 63) == 0) block[threadIdx.x >> 6] = r;
+}
+
 // The weight tiles wt[f / 64][c / 16][part][tap][(c / 8) % 2][f % 64][c % 8],
 // zero past cin and cout.
 __device__ __forceinline__ void put_unit(u4* wt, int nst, int f, int c8, int q, const float (&v)[8]) {
@@ -70,20 +102,24 @@ __device__ __forceinline__ void put_unit(u4* wt, int nst, int f, int c8, int q, 
         wt[(((int64_t(f / kF) * nst + c8 / kQ) * 3 + s) * 9 + q) * (kQ * kF) + (c8 % kQ) * kF + f % kF] = o[s];
 }
 
-// Dense weights w[f][c][9]: one unit (f, 8 channels, tap) per thread.
+// Dense weights w[f][c][9]: one unit (f, 8 channels, tap) per thread, 64
+// filters per blockIdx.y.
 __global__ __launch_bounds__(256) void k_split_dense(const float* __restrict__ w, int cin, int cout, int nst,
-                                                     int ftiles, u4* __restrict__ wt) {
-    const int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    const int64_t per = int64_t(nst) * kQ * 9;
-    const int f = int(e / per), u = int(e - f * per), c8 = u / 9, q = u - 9 * c8;
-    if (f >= ftiles * kF) return;
-    float v[8];
+                                                     u4* __restrict__ wt, uint32_t* __restrict__ flags) {
+    const int per = nst * kQ * 9, e = int(blockIdx.x * 256 + threadIdx.x);
+    const int fl = e / per, f = int(blockIdx.y) * kF + fl, u = e - fl * per, c8 = u / 9, q = u - 9 * c8;
+    Range range;
+    if (fl < kF) {
+        float v[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const int c = 8 * c8 + k;
-        v[k] = f < cout && c < cin ? w[(int64_t(f) * cin + c) * 9 + q] : 0.f;
+        for (int k = 0; k < 8; ++k) {
+            const int c = 8 * c8 + k;
+            v[k] = f < cout && c < cin ? w[(int64_t(f) * cin + c) * 9 + q] : 0.f;
+            range.add(v[k]);
+        }
+        put_unit(wt, nst, f, c8, q, v);
     }
-    put_unit(wt, nst, f, c8, q, v);
+    put_range(range, flags + int64_t(blockIdx.y) * (kFlags * nst) + blockIdx.x * 4);
 }
 
 // Compressed weights: 4 reordered filters x 128 channels per block, scattered
@@ -93,7 +129,7 @@ __global__ __launch_bounds__(256) void k_split_packed(const int32_t* __restrict_
                                                       const int32_t* __restrict__ cin_idx,
                                                       const uint8_t* __restrict__ pat_id,
                                                       const float* __restrict__ values, MGeo g, int nst,
-                                                      u4* __restrict__ wt) {
+                                                      u4* __restrict__ wt, uint32_t* __restrict__ flags) {
     __shared__ __align__(16) float t[kDF][9 * kDC];
     const int f0 = blockIdx.x * kDF, c0 = blockIdx.y * kDC;
     for (int e = threadIdx.x; e < kDF * 9 * kDC / 4; e += 256) reinterpret_cast<u4*>(t)[e] = u4{0, 0, 0, 0};
@@ -124,13 +160,17 @@ __global__ __launch_bounds__(256) void k_split_packed(const int32_t* __restrict_
         }
     }
     __syncthreads();
+    Range range;
     for (int e = threadIdx.x; e < kDF * 9 * kDC / 8; e += 256) {
         const int f = e % kDF, u = e / kDF, cg = u % (kDC / 8), q = u / (kDC / 8);
         if (c0 / kC + cg / kQ >= nst) continue;
         float v[8];
         __builtin_memcpy(v, &t[f][q * kDC + cg * 8], 32);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) range.add(v[k]);
         put_unit(wt, nst, f0 + f, c0 / 8 + cg, q, v);
     }
+    put_range(range, flags + int64_t(f0 / kF) * (kFlags * nst) + (blockIdx.y * (kF / kDF) + f0 % kF / kDF) * 4);
 }
 
 struct Packed {                                  // null perm: dense weights in `values`
@@ -143,7 +183,8 @@ struct Packed {                                  // null perm: dense weights in 
 
 template <int NT, bool ALIGNED>
 __global__ __launch_bounds__(kT, 2) void k_conv_split(const float* __restrict__ x, const u4* __restrict__ wtiles,
-                                                      Packed pk, const float* __restrict__ bias, MGeo g, int nst,
+                                                      const uint32_t* __restrict__ flags, int nflags, Packed pk,
+                                                      const float* __restrict__ bias, MGeo g, int nst,
                                                       float* __restrict__ y) {
     // 8 waves: 2 x 4 of 32 filters x NT / 4 pixels
     constexpr int NI = NT / 128;
@@ -164,6 +205,8 @@ __global__ __launch_bounds__(kT, 2) void k_conv_split(const float* __restrict__ 
     const int strip = pt / g.ptiles, o0 = (pt - strip * g.ptiles) * NT;
     const int j0 = strip * g.TW, f0 = ft * kF;
     const int plane = g.H * g.W, rowp = g.H + 1, per_img = g.OH * g.TW;
+    uint32_t wrange = 0;                                 // loaded first: the values' latency covers it
+    for (int e = lane; e < nflags; e += 64) wrange |= flags[int64_t(ft) * (kFlags * nst) + e];
 
     // padded row img * (H + 1) + i + 1 holds image row i
     auto prow = [&](int o, int& img, int& i, int& j) {
@@ -288,6 +331,24 @@ __global__ __launch_bounds__(kT, 2) void k_conv_split(const float* __restrict__ 
         for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
     const char* const abase = ldsA + ((lane >> 5) * kF + wf + (lane & 31)) * 16;
     fetch(0);
+    bool again = false;
+    wrange = wave_or(wrange);
+    if (wrange) {                                        // a look at the inputs
+        Range range;
+#pragma unroll 1
+        for (int st = 0; st < nst; ++st) {
+            fetch(st);
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) range.add(loff >= 0 ? xv[c][k] : 0.f);
+                range.add(halo && hloff >= 0 ? hv[c] : 0.f);
+            }
+        }
+        const uint32_t x = range.bits();
+        again = ((wrange & 1) && (x & 2)) || ((wrange & 2) && (x & 1));
+        fetch(0);
+    }
     __syncthreads();                                     // X zeroed
     for (int st = 0; st < nst; ++st) {
         stage();
@@ -323,7 +384,6 @@ __global__ __launch_bounds__(kT, 2) void k_conv_split(const float* __restrict__ 
         __syncthreads();
     }
 
-    bool again = false;
 #pragma unroll
     for (int t = 0; t < NI; ++t)
 #pragma unroll
@@ -400,13 +460,22 @@ bool plan_split(const ConvArgs& a, int m, MPlan& p) {
     return tile_plan(a, m, 128, p);
 }
 
-hipError_t launch(const MPlan& p, const Packed& pk, const ConvArgs& a, const u4* wt, hipStream_t s) {
+// The flags stand behind the tiles in the scratch.
+uint32_t* flags_of(const ConvArgs& a) {
+    const size_t tiles = size_t((a.cout + kF - 1) / kF) * size_t((a.cin + kC - 1) / kC) * kAU * 16;
+    return reinterpret_cast<uint32_t*>(static_cast<char*>(a.ws) + tiles);
+}
+
+// After k_split_* of nflags waves for each 64 filters.
+hipError_t launch(const MPlan& p, const Packed& pk, const ConvArgs& a, int nflags, hipStream_t s) {
+    const u4* const wt = static_cast<const u4*>(a.ws);
+    const uint32_t* const flags = flags_of(a);
     const int nst = (a.cin + kC - 1) / kC;
     const dim3 grid(unsigned((p.g.nblocks + 7) / 8 * 8));
     auto go = [&](auto nt, auto al) {
         hipLaunchKernelGGL((k_conv_split<decltype(nt)::value, decltype(al)::value != 0>), grid, dim3(kT), unsigned(p.lds),
-                           s, static_cast<const float*>(a.x), wt, pk, static_cast<const float*>(a.bias), p.g, nst,
-                           static_cast<float*>(a.y));
+                           s, static_cast<const float*>(a.x), wt, flags, nflags, pk, static_cast<const float*>(a.bias),
+                           p.g, nst, static_cast<float*>(a.y));
     };
     if (p.NT == 256)
         p.aligned ? go(IntC<256>{}, IntC<1>{}) : go(IntC<256>{}, IntC<0>{});
@@ -418,7 +487,7 @@ hipError_t launch(const MPlan& p, const Packed& pk, const ConvArgs& a, const u4*
 }  // namespace
 
 size_t split_tiles_bytes(int cout, int cin) {
-    return size_t((cout + kF - 1) / kF) * size_t((cin + kC - 1) / kC) * kAU * 16;
+    return size_t((cout + kF - 1) / kF) * size_t((cin + kC - 1) / kC) * (kAU * 16 + kFlags * 4);
 }
 
 bool conv_split_takes(const PatTable& tab, const ConvArgs& a) {
@@ -450,11 +519,11 @@ hipError_t launch_conv_split(const PatTable& tab, const PackedView& pk, const Co
     const int nst = (a.cin + kC - 1) / kC;
     const dim3 grid(unsigned(p.g.ftiles * kF / kDF), unsigned((a.cin + kDC - 1) / kDC));
     hipLaunchKernelGGL(k_split_packed, grid, dim3(256), 0, s, pk.filter_ptr, pk.cin_idx, pk.pat_id,
-                       static_cast<const float*>(pk.values), p.g, nst, static_cast<u4*>(a.ws));
+                       static_cast<const float*>(pk.values), p.g, nst, static_cast<u4*>(a.ws), flags_of(a));
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch(p, Packed{pk.filter_perm, pk.filter_ptr, pk.cin_idx, pk.pat_id, static_cast<const float*>(pk.values)},
-                  a, static_cast<const u4*>(a.ws), s);
+                  a, int(grid.y) * (kF / kDF) * 4, s);
 }
 
 // Layers of at least 16 channels and 32 filters (half a block's); `ws` holds
@@ -465,13 +534,12 @@ hipError_t launch_dense_split(const ConvArgs& a, const void* w, hipStream_t s) {
         !plan_split(a, 0, p))
         return hipErrorNotSupported;
     const int nst = (a.cin + kC - 1) / kC;
-    const int64_t units = int64_t(p.g.ftiles) * kF * nst * kQ * 9;
-    hipLaunchKernelGGL(k_split_dense, dim3(unsigned((units + 255) / 256)), dim3(256), 0, s, static_cast<const float*>(w),
-                       a.cin, a.cout, nst, p.g.ftiles, static_cast<u4*>(a.ws));
+    const dim3 grid(unsigned((kF * nst * kQ * 9 + 255) / 256), unsigned(p.g.ftiles));
+    hipLaunchKernelGGL(k_split_dense, grid, dim3(256), 0, s, static_cast<const float*>(w), a.cin, a.cout, nst,
+                       static_cast<u4*>(a.ws), flags_of(a));
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch(p, Packed{nullptr, nullptr, nullptr, nullptr, static_cast<const float*>(w)}, a,
-                  static_cast<const u4*>(a.ws), s);
+    return launch(p, Packed{nullptr, nullptr, nullptr, nullptr, static_cast<const float*>(w)}, a, int(grid.x) * 4, s);
 }
 
 }  // namespace psc

@@ -132,11 +132,12 @@ def _by_definition(x, w):
 
 
 @pytest.mark.parametrize("filters", [(7,), (1, 2, 3), (21, 30), (64,)], ids=str)
-@pytest.mark.parametrize("kind", ["weight", "x", "tiny"])
+@pytest.mark.parametrize("kind", ["weight", "x", "tiny", "tiny weights, large x", "large weights, tiny x"])
 def test_dense_values_that_bf16_parts_cannot_hold(kind, filters):
     """Any filter of a block alone brings the block to the fp32 sums: an
-    infinite weight, an infinite input beside zero columns, and weights whose
-    parts leave the range of bf16."""
+    infinite weight, an infinite input beside zero columns, weights whose
+    parts leave the range of bf16, and those against inputs (and the other way
+    round) that lift the sums back into it."""
     torch = torch_mod()
     n, cin, cout, h, w = DENSE[2]
     x, wt = inputs.normal_activations(1, (n, cin, h, w)), inputs.he_weights(2, cout, cin)
@@ -145,10 +146,15 @@ def test_dense_values_that_bf16_parts_cannot_hold(kind, filters):
             wt[f, 5, 0, 0], wt[f, 6, 2, 2] = np.inf, -3e38
         elif kind == "tiny":
             wt[f] *= np.float32(2.0 ** -120)
+        elif kind == "tiny weights, large x":
+            wt[f] *= np.float32(2.0 ** -121)
+        elif kind == "large weights, tiny x":
+            wt[f] *= np.float32(2.0 ** 60)
         else:
             wt[f, 9] = 0.0                          # 0 * inf
     if kind == "x":
         x[0, 9, 3, 3], x[1, 2, 0, 0], x[0, 4, 6, 6], x[1, 0, 2, 6] = np.inf, -np.inf, np.nan, 3.3e38
+    x *= np.float32({"tiny weights, large x": 2.0 ** 60, "large weights, tiny x": 2.0 ** -124}.get(kind, 1.0))
     y = torch.empty((n, cout, h, w), device="cuda")
     note("split dense %s %s" % (kind, filters))
     B.dense3x3_fwd(dev(x), dev(wt), y, ws=B.dense3x3_fwd_workspace(B.PSC_F32, cin, cout))
@@ -165,12 +171,13 @@ def test_dense_values_that_bf16_parts_cannot_hold(kind, filters):
     assert (np.abs(got[ok] - want[ok]) <= gamma(9 * cin + 1) * mag[ok] + 2 * 9 * cin * 2.0 ** -149).all()
 
 
-def test_sparse_filters_that_bf16_parts_cannot_hold():
+@pytest.mark.parametrize("lift", [1.0, 2.0 ** 60])
+def test_sparse_filters_that_bf16_parts_cannot_hold(lift):
     """The same for packed weights, filter by filter, against the
     one-output-per-lane kernel."""
     torch = torch_mod()
     n, cin, cout, h, w, drop, stride, m = SPARSE[3]
-    x = dev(inputs.normal_activations(6, (n, cin, h, w)))
+    x = dev(inputs.normal_activations(6, (n, cin, h, w)) * np.float32(lift))
     for f in (0, 1, 6, 11, 35, 63):
         wt = inputs.he_weights(5, cout, cin)
         masks = B.select_library(wt, m)
