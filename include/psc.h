@@ -218,10 +218,10 @@ psc_status psc_conv3x3_fwd_strided(const psc_layer *layer, const psc_packed *pac
  * or more add up to it, of a smaller one to within 2^-134; sums for which that
  * could matter, as well as those that are not finite, are taken again by fp32
  * multiply-adds, so that they keep the error bound of those (give or take
- * 2^-115 per product).  The buffer
- * holds nothing from one call to the next.  Calls on the same *packed, its
- * arrays unchanged, may share one buffer, also on several streams (each writes
- * the same bytes); any other calls that may overlap need one each. */
+ * 2^-115 per product).  The buffer holds nothing from one call to the next.
+ * Calls on the same *packed, its arrays unchanged, may share one buffer, also on
+ * several streams (each writes the same bytes); any other calls that may overlap
+ * need one each. */
 psc_status psc_conv3x3_workspace(const psc_layer *layer, size_t *bytes);
 /* *out = 1 where psc_conv3x3_fwd_ws with algo 0 runs the matrix-core kernel
  * (host only, arguments validated as by psc_conv3x3_config). */
@@ -307,8 +307,11 @@ psc_status psc_admm_residual(const float *d_z, const float *d_target, int64_t nu
  *                      g[n, o, h, w] * x[n, i, h + r - 1, w + s - 1]
  * and, if d_db is non-NULL, d_db[o] = sum of g[n, o, :, :]; fp32.  Layers of
  * at least 16 input channels run on the matrix cores (each value in three bf16
- * parts whose sum is exact), the others on the vector ALUs; partial sums are
- * added in a fixed order, so results are deterministic.  Workspace as for psc_conv3x3_bwd_weight
+ * parts, exact for a magnitude of 2^-110 or more and within 2^-134 below it; sums
+ * for which that could matter are taken again by fp32 multiply-adds, so that
+ * they keep the error bound of those, give or take 2^-105 per product), the
+ * others on the vector ALUs; partial sums are added in a fixed order, so results
+ * are deterministic.  Workspace as for psc_conv3x3_bwd_weight
  * (psc_dense3x3_bwd_weight_workspace bytes); x and g of more than 2 GiB
  * each return PSC_ERR_UNSUPPORTED. */
 psc_status psc_dense3x3_bwd_weight_workspace(int32_t n, int32_t cin, int32_t h, int32_t w,
@@ -375,8 +378,8 @@ psc_status psc_dense3x3_fwd(int32_t dtype, const void *d_x, int32_t n, int32_t c
  * psc_dense3x3_fwd_workspace bytes and 256-byte aligned (NULL: exactly that
  * call).  With it fp32 layers of at least 16 input channels and 32 filters run
  * on the 16-bit matrix cores, each value in three bf16 parts (as in
- * psc_conv3x3_fwd_ws).  The buffer holds nothing from one call to the next; calls that may overlap
- * need one each. */
+ * psc_conv3x3_fwd_ws).  The buffer holds nothing from one call to the next;
+ * calls that may overlap need one each. */
 psc_status psc_dense3x3_fwd_workspace(int32_t dtype, int32_t cin, int32_t cout, size_t *bytes);
 psc_status psc_dense3x3_fwd_ws(int32_t dtype, const void *d_x, int32_t n, int32_t cin,
                                int32_t h, int32_t w, const void *d_w, int32_t cout,

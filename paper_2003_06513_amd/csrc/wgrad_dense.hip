@@ -32,10 +32,13 @@
 // different rows.  Tiles are split over KS blocks whose partial sums go to KS
 // workspace slots, added afterwards in slot order (deterministic).
 //
-// Values that bf16 parts cannot hold, and zero columns that stand beside the
-// image: a block whose sums are not all finite, or that holds a nonzero sum
-// below 2^-90, computes its sums again with fp32 multiply-adds over the pixels
-// of the image alone.
+// Range.  Parts are whole down to 2^-133 (subnormals are kept): a value of 2^-110
+// or more is exactly the sum of its parts, a smaller one within 2^-134.  With
+// factors below 2^29, n products are so within n 2^-105 of those of fp32, 2^-25 n
+// of a sum of 2^-80.  A block with a sum that is not finite (also for the zero
+// columns that stand beside the image), a nonzero sum below 2^-80, or an fp32
+// value of 2^29 or more takes its sums again with fp32 multiply-adds over the
+// pixels of the image alone.
 #include "common.h"
 #include "launch.h"
 
@@ -75,7 +78,7 @@ __device__ __forceinline__ void raw_unit(Raw<DT>& v, int left, u4 (&parts)[DT ==
 }
 
 template <int DT>
-__device__ __forceinline__ void finish_unit(Raw<DT>& v, int left, u4 (&parts)[DT == DT_F32 ? 3 : 1]) {
+__device__ __forceinline__ void finish_unit(Raw<DT>& v, int left, u4 (&parts)[DT == DT_F32 ? 3 : 1], float& top) {
     if constexpr (DT == DT_F16) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) v.w[k] = left >= 2 * k + 2 ? v.w[k] : left == 2 * k + 1 ? v.w[k] & 0xffffu : 0;
@@ -86,6 +89,7 @@ __device__ __forceinline__ void finish_unit(Raw<DT>& v, int left, u4 (&parts)[DT
         for (int k = 0; k < 4; ++k) {
             f2 r = {2 * k < left ? __builtin_bit_cast(float, v.w[2 * k]) : 0.f,
                     2 * k + 1 < left ? __builtin_bit_cast(float, v.w[2 * k + 1]) : 0.f};
+            top = fmaxf(top, fmaxf(fabsf(r.x), fabsf(r.y)));
 #pragma unroll
             for (int s = 0; s < 3; ++s) {
                 w[s][k] = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, b2));
@@ -108,7 +112,8 @@ __device__ __forceinline__ int quot(int v, uint32_t m) { return m == 0xffffffffu
 template <int DT, int WT, bool WHOLE>
 __device__ __forceinline__ void stage_units(const typename Elt<DT>::T* p, int64_t total, int n, int H, int W,
                                             uint32_t h_m, int ch0, int chs, int row0, int grp0, int per,
-                                            uint32_t per_m, int live, int units, char* dst, int dst_plane) {
+                                            uint32_t per_m, int live, int units, char* dst, int dst_plane,
+                                            float& top) {
     using E = typename Elt<DT>::T;
     constexpr int NP = DT == DT_F32 ? 3 : 1, T = 32 * WT;
     constexpr int NB = 4;
@@ -142,7 +147,7 @@ __device__ __forceinline__ void stage_units(const typename Elt<DT>::T* p, int64_
                 if (u >= units) continue;
                 u4 parts[NP];
                 if constexpr (WHOLE) raw_unit<DT>(raw[k], left[k], parts);
-                else finish_unit<DT>(raw[k], left[k], parts);
+                else finish_unit<DT>(raw[k], left[k], parts, top);
 #pragma unroll
                 for (int s = 0; s < (WHOLE && NP > 1 ? 2 : NP); ++s)
                     *reinterpret_cast<u4*>(dst + s * dst_plane + (u * T + ch) * 16) = parts[s];
@@ -181,6 +186,7 @@ __device__ __forceinline__ void sum_again(const typename Elt<DT>::T* x, const ty
     const int uo = U > GT ? 1 : 0, last = RT * GT - 1, dy_plane = DU * T * 16, x_plane = (RT + 2) * U * T * 16;
     char* const ldsG = lds;
     char* const ldsX = lds + NP * dy_plane;
+    float top = 0.f;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wf = WT == 2 ? (wave & 1) * 32 : 0, wc = WT == 2 ? (wave >> 1) * 32 : 0;
     // the 8 columns of a unit
@@ -210,9 +216,9 @@ __device__ __forceinline__ void sum_again(const typename Elt<DT>::T* x, const ty
             const int rt = int(t / gtiles), grp0 = int(t - int64_t(rt) * gtiles) * GT;
             __syncthreads();
             stage_units<DT, WT, true>(g, int64_t(n) * cout * H * W, n, H, W, h_m, f0, cout, rt * RT, grp0, GT,
-                                      gt_m, last + 1, DU, ldsG, dy_plane);
+                                      gt_m, last + 1, DU, ldsG, dy_plane, top);
             stage_units<DT, WT, true>(x, int64_t(n) * cin * H * W, n, H, W, h_m, c0, cin, rt * RT - 1, grp0 - uo, U,
-                                      u_m, (RT + 2) * U, (RT + 2) * U, ldsX, x_plane);
+                                      u_m, (RT + 2) * U, (RT + 2) * U, ldsX, x_plane, top);
             __syncthreads();
 #pragma unroll 1
             for (int u = 0; u <= last; ++u) {
@@ -292,14 +298,14 @@ __global__ __launch_bounds__(256, 2) void k_wgrad_mfma(
     // summed from zero, every other time of -dy, and added to or subtracted
     // from the accumulator: 1.5e-7 there, as with fp32 multiply-adds
     constexpr int CH = DT == DT_F32 ? 1 : 2;
-    float sign = 1.f;
+    float sign = 1.f, top = 0.f;                         // top: the largest fp32 magnitude
     for (int64_t t = t0; t < t1; ++t) {
         const int rt = int(t / pl.gtiles), grp0 = int(t - int64_t(rt) * pl.gtiles) * GT, row0 = rt * pl.RT;
         if (t > t0) __syncthreads();
         stage_units<DT, WT, false>(g, g_total, n, H, W, pl.h_m, f0, cout, row0, grp0, GT, pl.gt_m, last + 1, pl.DU, ldsG,
-                                   dy_plane);
+                                   dy_plane, top);
         stage_units<DT, WT, false>(x, x_total, n, H, W, pl.h_m, c0, cin, row0 - 1, grp0 - uo, U, pl.u_m,
-                                   (pl.RT + 2) * U, (pl.RT + 2) * U, ldsX, x_plane);
+                                   (pl.RT + 2) * U, (pl.RT + 2) * U, ldsX, x_plane, top);
         __syncthreads();
         for (int k0 = 0; k0 < steps; k0 += CH) {
             sign = -sign;
@@ -394,7 +400,7 @@ __global__ __launch_bounds__(256, 2) void k_wgrad_mfma(
             }
         }
     }
-    bool again = false;
+    bool again = top >= 0x1p29f;
 #pragma unroll
     for (int q = 0; q < 9; ++q)
 #pragma unroll
@@ -402,8 +408,8 @@ __global__ __launch_bounds__(256, 2) void k_wgrad_mfma(
             if (owns(q, r)) {
                 const float v = acc[q][r];               // a bit cast of the element itself gives element 0
                 const uint32_t u = __builtin_bit_cast(uint32_t, v) << 1;
-                // 2 * 0x7f800000, and 2 * the bits of 2^-90 less one
-                again |= u >= 0xff000000u || (DT == DT_F32 && u - 1 < 2u * 0x12800000u - 1);
+                // 2 * 0x7f800000, and 2 * the bits of 2^-80 less one
+                again |= u >= 0xff000000u || (DT == DT_F32 && u - 1 < 2u * 0x17800000u - 1);
             }
     float* const dst = out + int64_t(ks) * cout * cin * 9;
     // asked before the store: a barrier after it would wait for it

@@ -168,3 +168,23 @@ def test_masked_non_finite(shape, dtype):
         ok = k & np.isfinite(want)
         assert f or ok.any()
         assert (np.abs(got[f][ok] - want[ok]) <= gamma(6 * n * h * w) * mag[f][ok] + 1e-37).all()
+
+
+@pytest.mark.parametrize("tiny", ["g", "x"])
+@pytest.mark.parametrize("channel", [0, 3, 7, 33])
+def test_tiny_values_against_large_ones(channel, tiny):
+    """One filter's gradient (one channel's input) whose parts leave the range
+    of bf16, against values that lift the sums back into it: the error stays
+    that of fp32 sums."""
+    n, cin, cout, h, w = 3, 40, 36, 6, 13
+    x, g = inputs.normal_activations(3, (n, cin, h, w)), inputs.normal_activations(4, (n, cout, h, w))
+    small, large = (g, x) if tiny == "g" else (x, g)
+    small[:, channel] *= np.float32(2.0 ** -124)
+    large *= np.float32(2.0 ** 60)
+    torch = torch_mod()
+    dw = torch.empty((cout, cin, 3, 3), device="cuda")
+    note("wgrad tiny %s, channel %d" % (tiny, channel))
+    B.dense3x3_bwd_weight(dev(x), dev(g), dw)
+    err = np.abs(dw.cpu().numpy().reshape(cout, cin, 9) - _wgrad(x, g))
+    bound = gamma(n * h * w) * _wgrad(np.abs(x), np.abs(g)) + n * h * w * 2.0 ** -105
+    assert (err <= bound).all(), float((err / bound).max())
