@@ -119,6 +119,7 @@ struct DenseWPlan {
     int64_t tiles;          // tiles in all
     int KS;                 // blocks the tiles are split over
     int lds;                // bytes
+    int64_t clocks;         // of a block, about
     uint32_t gt_m, u_m, h_m;    // 2^32 / GT, U and H + 1
 };
 bool dense_wgrad_mfma_plan(int n, int cin, int cout, int h, int w, int dtype, DenseWPlan* p);

@@ -51,6 +51,7 @@ typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 typedef __bf16 b8 __attribute__((ext_vector_type(8)));
 typedef __bf16 b2 __attribute__((ext_vector_type(2)));
 typedef float f2 __attribute__((ext_vector_type(2)));
+typedef uint16_t us2 __attribute__((ext_vector_type(2)));
 typedef float f16v __attribute__((ext_vector_type(16)));
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 
@@ -61,24 +62,12 @@ __device__ __forceinline__ f16v mfma(const u4& a, const u4& b, const f16v& c, In
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(b8, a), __builtin_bit_cast(b8, b), c, 0, 0, 0);
 }
 
-// 8 columns of a row: fp16 as they are, fp32 split into three bf16 parts
-// (raw_unit: as they are, in the first two); the columns from `left` on read
-// zero.
+// 8 columns of a row: fp16 as they are, fp32 split into three bf16 parts;
+// the columns from `left` on read zero.
 template <int DT> struct Raw { uint32_t w[DT == DT_F32 ? 8 : 4]; };
 
 template <int DT>
-__device__ __forceinline__ void raw_unit(Raw<DT>& v, int left, u4 (&parts)[DT == DT_F32 ? 3 : 1]) {
-#pragma unroll
-    for (int k = 0; k < 8 && DT == DT_F32; ++k) v.w[k] = k < left ? v.w[k] : 0;
-#pragma unroll
-    for (int k = 0; k < 4 && DT == DT_F16; ++k)
-        v.w[k] = left >= 2 * k + 2 ? v.w[k] : left == 2 * k + 1 ? v.w[k] & 0xffffu : 0;
-    parts[0] = u4{v.w[0], v.w[1], v.w[2], v.w[3]};
-    if constexpr (DT == DT_F32) parts[1] = u4{v.w[4], v.w[5], v.w[6], v.w[7]};
-}
-
-template <int DT>
-__device__ __forceinline__ void finish_unit(Raw<DT>& v, int left, u4 (&parts)[DT == DT_F32 ? 3 : 1], float& top) {
+__device__ __forceinline__ void finish_unit(Raw<DT>& v, int left, u4 (&parts)[DT == DT_F32 ? 3 : 1], us2& top) {
     if constexpr (DT == DT_F16) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) v.w[k] = left >= 2 * k + 2 ? v.w[k] : left == 2 * k + 1 ? v.w[k] & 0xffffu : 0;
@@ -89,13 +78,13 @@ __device__ __forceinline__ void finish_unit(Raw<DT>& v, int left, u4 (&parts)[DT
         for (int k = 0; k < 4; ++k) {
             f2 r = {2 * k < left ? __builtin_bit_cast(float, v.w[2 * k]) : 0.f,
                     2 * k + 1 < left ? __builtin_bit_cast(float, v.w[2 * k + 1]) : 0.f};
-            top = fmaxf(top, fmaxf(fabsf(r.x), fabsf(r.y)));
 #pragma unroll
             for (int s = 0; s < 3; ++s) {
                 w[s][k] = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, b2));
                 r.x -= __builtin_bit_cast(float, w[s][k] << 16);
                 r.y -= __builtin_bit_cast(float, w[s][k] & 0xffff0000u);
             }
+            top = __builtin_elementwise_max(top, __builtin_bit_cast(us2, w[0][k] & 0x7fff7fffu));
         }
 #pragma unroll
         for (int s = 0; s < 3; ++s) parts[s] = u4{w[s][0], w[s][1], w[s][2], w[s][3]};
@@ -105,63 +94,14 @@ __device__ __forceinline__ void finish_unit(Raw<DT>& v, int left, u4 (&parts)[DT
 // v / d for 0 <= v < 2^16 by m = 2^32 / d rounded up (all ones: d = 1)
 __device__ __forceinline__ int quot(int v, uint32_t m) { return m == 0xffffffffu ? v : int(__umulhi(uint32_t(v), m)); }
 
-// Stage `units` units of 8 columns for T channels (zeros from `live` on): 8
-// lanes take 8 channels of a unit (conflict-free LDS writes), the next 8 the
-// next unit (whole lines of 8 planes).  Four loads in flight a lane (7 to 10,
-// with both tensors in one batch, measured 5 to 10 % slower).
-template <int DT, int WT, bool WHOLE>
-__device__ __forceinline__ void stage_units(const typename Elt<DT>::T* p, int64_t total, int n, int H, int W,
-                                            uint32_t h_m, int ch0, int chs, int row0, int grp0, int per,
-                                            uint32_t per_m, int live, int units, char* dst, int dst_plane,
-                                            float& top) {
-    using E = typename Elt<DT>::T;
-    constexpr int NP = DT == DT_F32 ? 3 : 1, T = 32 * WT;
-    constexpr int NB = 4;
-    // image and row of padded row row0 (-1: the row before the first image)
-    const int im0 = row0 < 0 ? -1 : row0 / (H + 1), i0 = row0 - im0 * (H + 1), tid = threadIdx.x, plane = H * W;
-#pragma unroll
-    for (int h = 0; h < WT; ++h) {
-        const int ch = (tid & 7) + 8 * (tid >> 6) + 32 * h;
-        for (int u0 = (tid >> 3) & 7; u0 < units; u0 += 8 * NB) {
-            Raw<DT> raw[NB];
-            int left[NB];
-#pragma unroll
-            for (int k = 0; k < NB; ++k) {
-                const int u = u0 + 8 * k, r = quot(u, per_m), grp = grp0 + u - r * per;
-                const int d = quot(i0 + r, h_m), im = im0 + d, i = i0 + r - d * (H + 1) - 1;
-                const bool in = u < live && im >= 0 && i >= 0 && im < n && ch0 + ch < chs && grp >= 0 && 8 * grp < W;
-                left[k] = in ? W - 8 * grp : 0;
-                const int64_t at = in ? (int64_t(im) * chs + ch0 + ch) * plane + i * W + 8 * grp : 0;
-                if (at + 8 <= total) {
-                    __builtin_memcpy(raw[k].w, p + at, 8 * sizeof(E));
-                } else {                             // the end of the tensor
-                    E one[8];
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) one[e] = at + e < total ? p[at + e] : E(0);
-                    __builtin_memcpy(raw[k].w, one, sizeof one);
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < NB; ++k) {
-                const int u = u0 + 8 * k;
-                if (u >= units) continue;
-                u4 parts[NP];
-                if constexpr (WHOLE) raw_unit<DT>(raw[k], left[k], parts);
-                else finish_unit<DT>(raw[k], left[k], parts, top);
-#pragma unroll
-                for (int s = 0; s < (WHOLE && NP > 1 ? 2 : NP); ++s)
-                    *reinterpret_cast<u4*>(dst + s * dst_plane + (u * T + ch) * 16) = parts[s];
-            }
-        }
-    }
-}
-
 // The sizes of a call, kept in LDS for sum_again: in registers they would take
-// scalars from the hot loop (1 to 1.5 % of its time).
+// scalars from the hot loop (1 to 1.5 % of its time).  For the same reason
+// sum_again is a call (inlined: 512 @ 14x14 b64 fp16 183 us, 177 so) and comes
+// after the store.
 struct Sizes {
     int64_t tiles;
     int n, cin, H, W, cout, RT, GT, DU, U, gtiles, KS;
-    uint32_t gt_m, u_m, h_m;
+    uint32_t gt_m;
 };
 
 // The sums of a block that the matrix cores cannot give: the tiles staged
@@ -173,22 +113,36 @@ struct Sizes {
 // one by one, here): fp16 128 @ 28x28 b32 120, 1773, 126 and 120, 4055, 277; fp32
 // 256 @ 8x8 b256 255, 10245, 492 and 255, 12182, 558.
 template <int DT, int WT>
-__device__ __forceinline__ void sum_again(const typename Elt<DT>::T* x, const typename Elt<DT>::T* g, const Sizes& sz,
-                                          float* out, char* lds) {
+__device__ __attribute__((noinline, cold)) void sum_again(const typename Elt<DT>::T* x, const typename Elt<DT>::T* g,
+                                                          const Sizes& sz, float* out, char* lds) {
+    using E = typename Elt<DT>::T;
     constexpr int NP = DT == DT_F32 ? 3 : 1, T = 32 * WT;
     auto u = [](int v) { return __builtin_amdgcn_readfirstlane(v); };    // the same in every lane
     const int n = u(sz.n), cin = u(sz.cin), H = u(sz.H), W = u(sz.W), cout = u(sz.cout);
     const int RT = u(sz.RT), GT = u(sz.GT), DU = u(sz.DU), U = u(sz.U), gtiles = u(sz.gtiles), KS = u(sz.KS);
-    const uint32_t gt_m = u(sz.gt_m), u_m = u(sz.u_m), h_m = u(sz.h_m);
+    const uint32_t gt_m = u(sz.gt_m);
     const int f0 = blockIdx.x * T, c0 = blockIdx.y * T, ks = blockIdx.z;
     const int64_t t0 = sz.tiles * ks / KS, t1 = sz.tiles * (ks + 1) / KS;
     float* const dst = out + int64_t(ks) * cout * cin * 9;
     const int uo = U > GT ? 1 : 0, last = RT * GT - 1, dy_plane = DU * T * 16, x_plane = (RT + 2) * U * T * 16;
     char* const ldsG = lds;
     char* const ldsX = lds + NP * dy_plane;
-    float top = 0.f;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wf = WT == 2 ? (wave & 1) * 32 : 0, wc = WT == 2 ? (wave >> 1) * 32 : 0;
+    // the units of a tile as they are (fp32: columns 4 to 7 in the second plane)
+    auto stage = [&](const E* p, int ch0, int chs, int row0, int grp0, int per, int units, char* to, int plane_bytes) {
+        for (int e = int(threadIdx.x); e < units * T; e += 256) {
+            const int u = e / T, ch = e - u * T, r = u / per, R = row0 + r, col = 8 * (grp0 + u - r * per);
+            const int im = R < 0 ? -1 : R / (H + 1), i = R - im * (H + 1) - 1;
+            const bool in = im >= 0 && im < n && i >= 0 && ch0 + ch < chs && col >= 0;
+            const int64_t at = in ? (int64_t(im) * chs + ch0 + ch) * (H * W) + i * W + col : 0;
+            E v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = in && col + k < W ? p[at + k] : E(0);
+            __builtin_memcpy(to + e * 16, v, 16);
+            if constexpr (DT == DT_F32) __builtin_memcpy(to + plane_bytes + e * 16, v + 4, 16);
+        }
+    };
     // the 8 columns of a unit
     auto columns = [&](const char* unit, int plane_bytes, float* v) {
         const u4 lo = *reinterpret_cast<const u4*>(unit);
@@ -215,10 +169,8 @@ __device__ __forceinline__ void sum_again(const typename Elt<DT>::T* x, const ty
         for (int64_t t = t0; t < t1; ++t) {
             const int rt = int(t / gtiles), grp0 = int(t - int64_t(rt) * gtiles) * GT;
             __syncthreads();
-            stage_units<DT, WT, true>(g, int64_t(n) * cout * H * W, n, H, W, h_m, f0, cout, rt * RT, grp0, GT,
-                                      gt_m, last + 1, DU, ldsG, dy_plane, top);
-            stage_units<DT, WT, true>(x, int64_t(n) * cin * H * W, n, H, W, h_m, c0, cin, rt * RT - 1, grp0 - uo, U,
-                                      u_m, (RT + 2) * U, (RT + 2) * U, ldsX, x_plane, top);
+            stage(g, f0, cout, rt * RT, grp0, GT, last + 1, ldsG, dy_plane);
+            stage(x, c0, cin, rt * RT - 1, grp0 - uo, U, (RT + 2) * U, ldsX, x_plane);
             __syncthreads();
 #pragma unroll 1
             for (int u = 0; u <= last; ++u) {
@@ -271,7 +223,7 @@ __global__ __launch_bounds__(256, 2) void k_wgrad_mfma(
     if (threadIdx.x == 0) {
         sizes.n = n, sizes.cin = cin, sizes.H = H, sizes.W = W, sizes.cout = cout;
         sizes.RT = pl.RT, sizes.GT = pl.GT, sizes.DU = pl.DU, sizes.U = pl.U, sizes.gtiles = pl.gtiles, sizes.KS = pl.KS;
-        sizes.tiles = pl.tiles, sizes.gt_m = pl.gt_m, sizes.u_m = pl.u_m, sizes.h_m = pl.h_m;
+        sizes.tiles = pl.tiles, sizes.gt_m = pl.gt_m;
     }
     const int GT = pl.GT, U = pl.U, uo = U > GT ? 1 : 0;
     const int dy_plane = pl.DU * T * 16, x_plane = (pl.RT + 2) * U * T * 16;
@@ -282,6 +234,49 @@ __global__ __launch_bounds__(256, 2) void k_wgrad_mfma(
     const int64_t t0 = pl.tiles * ks / pl.KS, t1 = pl.tiles * (ks + 1) / pl.KS;
     const int plane = H * W;
     const int64_t g_total = int64_t(n) * cout * plane, x_total = int64_t(n) * cin * plane;
+
+    us2 top = {0, 0};                                    // the largest magnitudes of fp32 values, as bf16
+    using E = typename Elt<DT>::T;
+    auto stage = [&](const E* p, int64_t total, int ch0, int chs, int row0, int grp0, int per, uint32_t per_m,
+                     int live, int units, char* dst, int dst_plane) {
+        constexpr int NB = 4;
+        // image and row of padded row row0 (-1: the row before the first image)
+        const int im0 = row0 < 0 ? -1 : row0 / (H + 1), i0 = row0 - im0 * (H + 1);
+#pragma unroll
+        for (int h = 0; h < WT; ++h) {
+            const int ch = (tid & 7) + 8 * (tid >> 6) + 32 * h;
+            for (int u0 = (tid >> 3) & 7; u0 < units; u0 += 8 * NB) {
+                Raw<DT> raw[NB];
+                int left[NB];
+#pragma unroll
+                for (int k = 0; k < NB; ++k) {
+                    const int u = u0 + 8 * k, r = quot(u, per_m), grp = grp0 + u - r * per;
+                    const int d = quot(i0 + r, pl.h_m), im = im0 + d, i = i0 + r - d * (H + 1) - 1;
+                    const bool in = u < live && im >= 0 && i >= 0 && im < n && ch0 + ch < chs && grp >= 0 && 8 * grp < W;
+                    left[k] = in ? W - 8 * grp : 0;
+                    const int64_t at = in ? (int64_t(im) * chs + ch0 + ch) * plane + i * W + 8 * grp : 0;
+                    if (at + 8 <= total) {
+                        __builtin_memcpy(raw[k].w, p + at, 8 * sizeof(E));
+                    } else {                             // the end of the tensor
+                        E one[8];
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) one[e] = at + e < total ? p[at + e] : E(0);
+                        __builtin_memcpy(raw[k].w, one, sizeof one);
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < NB; ++k) {
+                    const int u = u0 + 8 * k;
+                    if (u >= units) continue;
+                    u4 parts[NP];
+                    finish_unit<DT>(raw[k], left[k], parts, top);
+#pragma unroll
+                    for (int s = 0; s < NP; ++s)
+                        *reinterpret_cast<u4*>(dst + s * dst_plane + (u * T + ch) * 16) = parts[s];
+                }
+            }
+        }
+    };
 
     // this half-wave's filters, channels and units
     const int wf = WT == 2 ? (wave & 1) * 32 : 0, wc = WT == 2 ? (wave >> 1) * 32 : 0;
@@ -298,14 +293,12 @@ __global__ __launch_bounds__(256, 2) void k_wgrad_mfma(
     // summed from zero, every other time of -dy, and added to or subtracted
     // from the accumulator: 1.5e-7 there, as with fp32 multiply-adds
     constexpr int CH = DT == DT_F32 ? 1 : 2;
-    float sign = 1.f, top = 0.f;                         // top: the largest fp32 magnitude
+    float sign = 1.f;
     for (int64_t t = t0; t < t1; ++t) {
         const int rt = int(t / pl.gtiles), grp0 = int(t - int64_t(rt) * pl.gtiles) * GT, row0 = rt * pl.RT;
         if (t > t0) __syncthreads();
-        stage_units<DT, WT, false>(g, g_total, n, H, W, pl.h_m, f0, cout, row0, grp0, GT, pl.gt_m, last + 1, pl.DU, ldsG,
-                                   dy_plane, top);
-        stage_units<DT, WT, false>(x, x_total, n, H, W, pl.h_m, c0, cin, row0 - 1, grp0 - uo, U, pl.u_m,
-                                   (pl.RT + 2) * U, (pl.RT + 2) * U, ldsX, x_plane, top);
+        stage(g, g_total, f0, cout, row0, grp0, GT, pl.gt_m, last + 1, pl.DU, ldsG, dy_plane);
+        stage(x, x_total, c0, cin, row0 - 1, grp0 - uo, U, pl.u_m, (pl.RT + 2) * U, (pl.RT + 2) * U, ldsX, x_plane);
         __syncthreads();
         for (int k0 = 0; k0 < steps; k0 += CH) {
             sign = -sign;
@@ -400,7 +393,7 @@ __global__ __launch_bounds__(256, 2) void k_wgrad_mfma(
             }
         }
     }
-    bool again = top >= 0x1p29f;
+    bool again = top.x >= 0x4e00 || top.y >= 0x4e00;     // 2^29
 #pragma unroll
     for (int q = 0; q < 9; ++q)
 #pragma unroll
@@ -496,7 +489,7 @@ bool dense_wgrad_mfma_plan(int n, int cin, int cout, int h, int w, int dtype, De
     // 64 x 64 tiles only where those alone give every CU a quarter of a block,
     // and (fp32, whose three parts fill the LDS) where a row is one group of
     // columns: 512 -> 512 @ 4x4 b256, fp16: 120 us, against 138 in 32 x 32
-    q.WT = big >= 64 && (dtype == DT_F16 ? n * h * w >= 4096 : w <= 8) ? 2 : 1;
+    q.WT = big >= 64 && (dtype == DT_F16 ? int64_t(n) * h * w >= 4096 : w <= 8) ? 2 : 1;
     const int T = 32 * q.WT, NS = q.WT == 2 ? 2 : 8;
     q.fb = (cout + T - 1) / T;
     q.cb = (cin + T - 1) / T;
@@ -543,6 +536,7 @@ bool dense_wgrad_mfma_plan(int n, int cin, int cout, int h, int w, int dtype, De
             if (cost < least_cost) least_cost = cost, best = r;
         }
         rt = best;
+        q.clocks = least_cost;
     }
     q.RT = int(rt);
     q.DU = int((rt * q.GT + NS - 1) / NS * NS);
