@@ -292,15 +292,30 @@ static size_t wgrad_part_bytes(const WGeo& g, int64_t nk, bool dense) {
 // matrix cores.  At batch 1 the masked kernels are bound by load latency
 // (fp16 512 @ 14x14: 41 us, dense 31; fp32 256 @ 56x56: 72, dense 59).  At
 // larger batches their time falls with the kernels kept and the dense one's
-// does not: at 40 % kept and full groups of 8 columns it takes about half in
-// fp16 (64 @ 32x32 b256 304 -> 105 us) and 0.6 in fp32 (256 @ 8x8 b256
-// 254 -> 157), which puts the lines at 18 and 25 % of the kernels.
+// does not.  fp16: at 40 % kept and full groups of 8 columns the dense one takes
+// about half (64 @ 32x32 b256 304 -> 105 us), which puts the line at 18 % of the
+// kernels, the padding of channels, filters and columns counted.
+// fp32, with six times the MFMAs: 25 % in the same way, and estimates in us
+// (without db) on top for calls that are far from filling the chip: 12, a
+// block's clocks and the traffic of its slots, against the masked kernels'
+// nonzero multiply-adds, slower on few pixels, narrow rows and rows of odd
+// widths.  Measured both ways on 30 layers at 10 to 100 % kept, the worst choice
+// 18 % off; where the dense one still wins and where it no longer does (us,
+// masked first): 64 @ 56x56 b2 100 % 58, 43 and 40 % 40, 43; 512 @ 14x14 b2 40 %
+// 48, 44 and 30 % 40, 44; 64 @ 14x14 b16 100 % 35, 34 and 40 % 30, 34; 32 @ 28x28
+// b4 100 % 31, 34; 16->64 @ 112x112 b8 60 % 78, 97.
 static bool masked_via_dense(int n, int cin, int cout, int h, int w, int64_t keep, int dtype, DenseWPlan* dp) {
     if (!dense_wgrad_mfma_plan(n, cin, cout, h, w, dtype, dp)) return false;
-    // the padding of channels, filters and columns counts as dense work
+    if (n == 1) return true;
     const int64_t cols = (w + 7) / 8 * 8, line = dtype == DT_F16 ? 18 : 25;
     const int64_t pairs = int64_t((cin + 31) / 32 * 32) * ((cout + 31) / 32 * 32);
-    return n == 1 || double(100 * keep) * w >= double(line * pairs) * cols;
+    if (double(100 * keep) * w < double(line * pairs) * cols) return false;
+    if (dtype == DT_F16) return true;
+    const double px = double(n) * h * w, slots = double(dense_wgrad_mfma_workspace(*dp, cin, cout));
+    const double dense_us = 12.0 + 1.25 * double(dp->clocks) / 2400.0 + 0.6e-6 * slots;
+    const bool odd = w % 4 && w != 7 && w != 14;
+    const double base = dp->fb * dp->cb == 1 ? 14.0 : odd ? 30.0 : 22.0, rate = (odd ? 0.44 : 0.14) + 20.0 / px;
+    return dense_us <= base + rate * 4e-6 * px * double(keep) * 8.0 / (w < 8 ? w : 8);
 }
 
 size_t wgrad_workspace_bytes(int n, int cin, int cout, int h, int w, int64_t nk, bool dense, int dtype) {

@@ -122,7 +122,7 @@ def test_values_that_bf16_parts_cannot_hold(scale):
 
 # n, cin, cout, h, w: 32-wide blocks (rows whole and in parts, ragged), and
 # 64-wide ones (at least 64 of them, and 4096 pixels)
-NON_FINITE = [(5, 33, 70, 9, 13), (2, 48, 36, 5, 130), (64, 512, 500, 8, 8)]
+NON_FINITE = [(40, 33, 70, 9, 13), (3, 48, 36, 20, 130), (64, 512, 500, 8, 8)]
 
 
 @pytest.mark.parametrize("dtype", [np.float16, np.float32])
@@ -143,7 +143,7 @@ def test_masked_non_finite(shape, dtype):
     dv = torch.empty(4 * cout * cin, device="cuda")
     note("masked wgrad non-finite %s %s" % (shape, np.dtype(dtype).name))
     ws = B.conv3x3_bwd_weight(prep.layer, prep.packed, dev(x), dev(g), dv)
-    assert ws.numel() >= 36 * cout * cin        # a slot of the dense gradient
+    assert ws.numel() % (36 * cout * cin) == 0  # slots of the dense gradient
     pk = prep.packed.to_host()
     pos = np.repeat(np.arange(cout), np.diff(pk["filter_ptr"]))
     bits = np.array([[b for b in range(9) if (int(c) >> b) & 1] for c in masks])[pk["pat_id"]]
@@ -188,3 +188,40 @@ def test_tiny_values_against_large_ones(channel, tiny):
     err = np.abs(dw.cpu().numpy().reshape(cout, cin, 9) - _wgrad(x, g))
     bound = gamma(n * h * w) * _wgrad(np.abs(x), np.abs(g)) + n * h * w * 2.0 ** -105
     assert (err <= bound).all(), float((err / bound).max())
+
+
+# 32-wide blocks (ragged, rows whole and in parts), and 64-wide ones (at least
+# 64 of them and 4096 pixels in fp16; rows of one group in fp32), also ragged
+ROUTED = [(40, 60, 70, 9, 13), (3, 48, 36, 20, 130), (256, 64, 64, 7, 8), (64, 512, 512, 8, 8), (40, 500, 460, 10, 13),
+          (70, 460, 500, 9, 7)]
+
+
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+@pytest.mark.parametrize("shape", ROUTED, ids=["x".join(map(str, s)) for s in ROUTED])
+def test_masked_on_matrix_cores(shape, dtype):
+    """The masked gradient of calls that take the dense one (the workspace is
+    whole slots of it), for some filters of each block."""
+    torch = torch_mod()
+    n, cin, cout, h, w = shape
+    x = inputs.normal_activations(5, (n, cin, h, w), dtype)
+    g = inputs.normal_activations(6, (n, cout, h, w), dtype)
+    wt = inputs.he_weights(7, cout, cin, dtype)
+    masks = B.select_library(wt, 8)
+    keep = inputs.keep_after_drop(cout * cin, 20)
+    prep = B.prepare(dev(wt), masks, keep)
+    dv = torch.empty(4 * keep, device="cuda")
+    note("masked wgrad routed %s %s" % (shape, np.dtype(dtype).name))
+    ws = B.conv3x3_bwd_weight(prep.layer, prep.packed, dev(x), dev(g), dv)
+    bias = -(-n * h * w // 8192) * 4 * cout if n * h * w > 8192 else 0
+    assert (ws.numel() - bias) % (36 * cout * cin) == 0 and (ws.numel() - bias) % (16 * keep) != 0
+    pk = prep.packed.to_host()
+    pos = np.repeat(np.arange(cout), np.diff(pk["filter_ptr"]))
+    bits = np.array([[b for b in range(9) if (int(c) >> b) & 1] for c in masks])[pk["pat_id"]]
+    f = pk["filter_perm"][pos]
+    some = [c for c in sorted({0, 5, 31, 32, 38, 63, 64, 200, cout - 1}) if c < cout]
+    on = np.isin(f, some)
+    at = (np.searchsorted(some, f[on])[:, None], pk["cin_idx"][on][:, None], bits[on])
+    gs = np.ascontiguousarray(g[:, some])
+    err = np.abs(dv.cpu().numpy().reshape(-1, 4)[on] - _wgrad(x, gs)[at])
+    bound = gamma(6 * n * h * w) * _wgrad(np.abs(x), np.abs(gs))[at] + 1e-37
+    assert on.any() and (err <= bound).all(), float((err / bound).max())
