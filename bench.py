@@ -256,12 +256,13 @@ def layer_table(net, miopen):
         lay, prep = L["lay"], L["prep"]
         med, p10, p90, mean = time_launches(lambda: net.launch(L))
         nz = net.nz_flops(li)
+        mfma = L["mfma"] and not L["fused"]         # then the vector plan has not run
         row = dict(layer=lay.name, cin=lay.cin, cout=lay.cout, h=lay.h, w=lay.w, stride=lay.stride, keep=lay.keep,
                    fused_pool=bool(L["fused"]), ms=round(med, 5), p10=round(p10, 5), p90=round(p90, 5),
                    mean_ms=round(mean, 5), nz_gflops=round(nz / (med * 1e-3) / 1e9, 1),
-                   kernel="mfma" if L["mfma"] and not L["fused"] else
+                   kernel="mfma" if mfma else
                    ["stream", "wide", "simple", "stride2", "rows"][L["cfg"]["kernel"]] + ("-staged" if L["cfg"]["staged"] else ""),
-                   R=L["cfg"]["rows_per_lane"], KS=L["cfg"]["shares"])
+                   R=None if mfma else L["cfg"]["rows_per_lane"], KS=None if mfma else L["cfg"]["shares"])
         if "fusion_us" in L:
             row["pool_separate_fused_us"] = L["fusion_us"]
         if miopen:
@@ -425,7 +426,7 @@ def measure_admm(wl, iters=10, parts=True):
     z = st._bufs["z"]
     dense_fl = 18.0 * wl.batch * wl.layer.h * wl.layer.w * wl.layer.cin * wl.layer.cout
     parts = {
-        "dense_fwd": time_launches(lambda: B.dense3x3_fwd(x, st.w, z, bias=st.b), warm=3, samples=10, reps=2)[0],
+        "dense_fwd": time_launches(lambda: B.dense3x3_fwd(x, st.w, z, bias=st.b, ws=st.ws_dense), warm=3, samples=10, reps=2)[0],
         "residual": time_launches(lambda: B.admm_residual(z, tgt, scale, st._bufs["g"], st.loss, st.ws_res),
                                   warm=3, samples=10, reps=2)[0],
         "dense_wgrad": time_launches(lambda: B.dense3x3_bwd_weight(x, st._bufs["g"], st.dw, st.db,
