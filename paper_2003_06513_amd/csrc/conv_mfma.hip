@@ -11,8 +11,8 @@
 // staged input feeds all filters of the block.  The vector kernels are bound
 // by the vector-memory path that brings each kernel's rows to the registers.
 // Measured (fp16, 60 % dropped, us a call, vector kernel first):
-// 512 @ 28x28 b64 866 -> 247, 512 @ 7x7 b32 42.5 -> 29.8, 256 @ 14x14 b32
-// 36.1 -> 22.7, 128 @ 28x28 b32 48.0 -> 20.3, 64 @ 56x56 b32 49.4 -> 24.0.
+// 512 @ 28x28 b64 866 -> 250, 512 @ 7x7 b32 42.5 -> 29.1, 256 @ 14x14 b32
+// 36.1 -> 22.7, 128 @ 28x28 b32 48.0 -> 20.5, 64 @ 56x56 b32 49.4 -> 24.0.
 // Decoding inside the convolution instead (each block scattering its filters'
 // kernels into its weight tile) measured 342 on the first and 62 on the
 // second: the scatter repeats for every pixel tile.

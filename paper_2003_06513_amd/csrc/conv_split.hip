@@ -5,12 +5,12 @@
 // Every fp32 value is split into three bf16 parts, a = a1 + a2 + a3, each the
 // rounding of what the ones before leave (24 bits: the sum is exact).  Of the
 // nine products a_i b_j the six with i + j <= 4 are taken, by
-// v_mfma_f32_32x32x16_bf16; what is dropped is below 2^-26 of a product.  Six
-// of those MFMAs cost 0.38 of the fp32 MFMAs of the same product.  The six
-// products of 16 channels at one tap are summed from the smallest up, from
-// zero, every other time of -w; only that sum meets the accumulator (one
-// rounding per 16 channels and tap, and a lean of the matrix cores' sums to one
-// side cancels).
+// v_mfma_f32_32x32x16_bf16; what is dropped is below 2^-24 of a product
+// (|a2| <= 2^-8 |a|, |a3| <= 2^-17 |a|; one rounding of fp32).  Six of those
+// MFMAs cost 0.38 of the fp32 MFMAs of the same product.  The six products of 16
+// channels at one tap are summed from the smallest up, from zero, every other
+// time of -w; only that sum meets the accumulator (one rounding per 16 channels
+// and tap, and a lean of the matrix cores' sums to one side cancels).
 //
 // The layout is that of the fp16 kernel: k_split_* write the weights of 64
 // filters x 16 channels as three planes in LDS order, and a block of 8 waves

@@ -9,13 +9,13 @@
 // sums).  fp32 values split into three bf16 parts, a = a1 + a2 + a3 (each the
 // rounding of what the ones before leave, so the sum is exact), and six of the
 // nine products a_i b_j, i + j <= 4, by v_mfma_f32_32x32x16_bf16; what is
-// dropped is below 2^-26 of a product.  Six of those cost 0.38 of the fp32
-// MFMAs they replace.  The six products of 16 pixels are summed from the
-// smallest up, from zero, and only that sum is added to the accumulator: one
-// rounding at the accumulator's size per 16 pixels, where the fp32 MFMA had
-// four.
+// dropped is below 2^-24 of a product (|a2| <= 2^-8 |a|, |a3| <= 2^-17 |a|; one
+// rounding of fp32).  Six of those cost 0.38 of the fp32 MFMAs they replace.
+// The six products of 16 pixels are summed from the smallest up, from zero, and
+// only that sum is added to the accumulator: one rounding at the accumulator's
+// size per 16 pixels, where the fp32 MFMA had four.
 // Measured (dv + db of a layer, 60 % of the kernels dropped, vector kernels
-// first, us): fp16 128 @ 28x28 b32 118 -> 57, 64 @ 32x32 b256 304 -> 104;
+// first, us): fp16 128 @ 28x28 b32 118 -> 52, 64 @ 32x32 b256 304 -> 104;
 // fp32 256 @ 8x8 b256 254 -> 157, 64 @ 56x56 b32 148 -> 116; dense fp32
 // 64 @ 32x32 b32 (fp32 MFMA first) 57 -> 53.
 //

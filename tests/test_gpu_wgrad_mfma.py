@@ -2,7 +2,8 @@
 against a float64 sum on the CPU: dense (fp32, from three bf16 parts) and
 masked (fp16 and fp32).  The bound per entry is gamma_n times the sum of the
 absolute products, n the number of pixels (each of the n products is exact or
-within 2^-26, each addition rounds once)."""
+within 2^-24, one rounding; each addition rounds once; what the parts drop and
+the slots' sums stay within the factor that the tests give)."""
 import numpy as np
 import pytest
 
