@@ -23,11 +23,12 @@
 //   X[c / 8][position][8]       the input rows the tile needs, channels innermost,
 //   A[c / 32][tap][c / 8][filter][8]   the weights,
 // both in 16-byte units that neighbouring lanes read from neighbouring
-// addresses (no bank conflicts).  A tap is an offset of positions, so one X
-// tile serves all nine.  The next stage's values load into registers while
-// the MFMAs of this one run; the large tiles are bound by LDS reads (4 KB for
-// 4 MFMAs of a wave, the 128 B a clock that LDS gives), the small ones by the
-// latency of their chain of stages.
+// addresses.  A tap is an offset of positions, so one X tile serves all nine.
+// The next stage's values load into registers while the MFMAs of this one run.
+// Counters (ResNet-50 layers, b32): MFMAs busy 12 to 16 % of the time, HBM 0.8 to
+// 2 TB/s, 1.1 to 1.6 conflict clocks per active LDS clock: it is bound by its
+// chain of stages, each a register round trip between two barriers with 4 KB of
+// LDS reads for 4 MFMAs of a wave.
 //
 // Infinities and NaNs: the dense tile multiplies pruned weights (zero) by
 // every staged input, which must not turn a non-finite input that no kept
